@@ -1,10 +1,12 @@
 // Dense contractions of the exact block: out = epi(A W^T + bias) with A [M, K] (rows
 // through a RowMap), W [N, K] (both K-contiguous), fp32 accumulation.
 //
-// bf16: v_mfma_f32_32x32x16_bf16 on 256x256 or 128x128 workgroup tiles, fed from LDS.
-// The main kernel streams operands global -> LDS directly through a multi-stage ring; a
-// register-staged kernel (padded LDS rows, double buffer) covers K % 32 != 0.
+// bf16: 256-row workgroup tiles of v_mfma_f32_16x16x32_bf16 (k_gemm_pp) where the grid fills
+// the card or K % 64 != 0, 128-row tiles of v_mfma_f32_32x32x16_bf16 (k_gemm_dl) on small
+// grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
+// rows, double buffer) covers K <= 128 off the 64 grid (the patch embedding).
 // fp32: 64x64x16 tile of plain FMAs (the small fp32 workload is launch-bound).
+#include <algorithm>
 #include "dev_common.h"
 
 namespace ff {
@@ -50,14 +52,33 @@ constexpr int epi_lds_elems() { return NW * 32 * (WN + 4) * 2; }
 // fetched by the storing lanes with a lane shuffle.  N % 8 == 0: a piece is in range as a
 // whole.  LDS use is wave-private: the caller must have retired the main loop's LDS reads
 // of all waves (barrier) before the first call.
-template <int TM, int TN, int EPI, bool OUT_F32, bool RES_F32>
-__device__ __forceinline__ void epilogue_block(const GemmArgs a, int rbase, int cbase, const f32x16_t (&acc)[TM][TN], uint16_t* lds) {
+//
+// Accumulator layouts: pieces of 4 consecutive output columns held by a lane, piece p of
+// 32-row block i at row row() and column col() of the block.
+template <int TM_, int TN_>
+struct Acc32 {   // 32x32 tiles: lane l row l%32, columns 32 j + 8 q + 4 (l/32) + 0..3
+  static constexpr int TM = TM_, WN = TN_ * 32, P = TN_ * 4;
+  f32x16_t t[TM_][TN_];
+  __device__ __forceinline__ static int row(int, int lane) { return lane & 31; }
+  __device__ __forceinline__ static int col(int p, int lane) { return p * 8 + (lane >> 5) * 4; }
+  __device__ __forceinline__ float get(int i, int p, int e) const { return t[i][p / 4][4 * (p % 4) + e]; }
+};
+template <int TM_, int TN_>
+struct Acc16 {   // 16x16 tiles (two per 32-row block): lane l row l%16, columns 16 j + 4 (l/16) + 0..3
+  static constexpr int TM = TM_ / 2, WN = TN_ * 16, P = TN_ * 2;
+  f32x4_t t[TM_][TN_];
+  __device__ __forceinline__ static int row(int p, int lane) { return (p / TN_) * 16 + (lane & 15); }
+  __device__ __forceinline__ static int col(int p, int lane) { return (p % TN_) * 16 + (lane >> 4) * 4; }
+  __device__ __forceinline__ float get(int i, int p, int e) const { return t[2 * i + p / TN_][p % TN_][e]; }
+};
+template <int EPI, bool OUT_F32, bool RES_F32, class ACC>
+__device__ __forceinline__ void epilogue_block(const GemmArgs a, int rbase, int cbase, const ACC& acc, uint16_t* lds) {
   constexpr bool kF32 = OUT_F32 || EPI == EPI_GATED;
-  constexpr int WN = TN * 32, CPR = WN / 8, RPP = 64 / CPR, NPASS = (32 + RPP - 1) / RPP;
+  constexpr int TM = ACC::TM, WN = ACC::WN, CPR = WN / 8, RPP = 64 / CPR, NPASS = (32 + RPP - 1) / RPP;
   constexpr int LDW = kF32 ? WN + 4 : WN + 8;   // row pitch in staged elements
   static_assert(CPR <= 64, "row wider than a wavefront's pieces");
   constexpr bool kCache = EPI == EPI_GATED && !OUT_F32;
-  const int lane = threadIdx.x & 63, fr = lane & 31, fh = lane >> 5;
+  const int lane = threadIdx.x & 63, fr = lane & 31;
   const uint16_t* bias = reinterpret_cast<const uint16_t*>(a.bias);
   const bool gelu = EPI == EPI_BIAS_GELU || (EPI == EPI_BIAS_OR_GELU && a.epi == EPI_BIAS_GELU);
   float* lf = reinterpret_cast<float*>(lds);
@@ -67,24 +88,22 @@ __device__ __forceinline__ void epilogue_block(const GemmArgs a, int rbase, int 
     const int prow = a.omap.phys(rmine < a.M ? rmine : 0);
     const int srow = EPI == EPI_GATED ? a.omap.sample(rmine < a.M ? rmine : 0) : 0;
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int p = 0; p < ACC::P; ++p) {
+      const int pr = ACC::row(p, lane), pc = ACC::col(p, lane), c = cbase + pc;
+      const u32x2_t bw = *reinterpret_cast<const u32x2_t*>(bias + (c < a.N ? c : 0));
+      float v[4] = {acc.get(i, p, 0) + __uint_as_float(bw[0] << 16), acc.get(i, p, 1) + __uint_as_float(bw[0] & 0xffff0000u),
+                    acc.get(i, p, 2) + __uint_as_float(bw[1] << 16), acc.get(i, p, 3) + __uint_as_float(bw[1] & 0xffff0000u)};
+      if (gelu) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = cbase + j * 32 + q * 8 + fh * 4;
-        const u32x2_t bw = *reinterpret_cast<const u32x2_t*>(bias + (c < a.N ? c : 0));
-        float v[4] = {acc[i][j][4 * q] + __uint_as_float(bw[0] << 16), acc[i][j][4 * q + 1] + __uint_as_float(bw[0] & 0xffff0000u),
-                      acc[i][j][4 * q + 2] + __uint_as_float(bw[1] << 16), acc[i][j][4 * q + 3] + __uint_as_float(bw[1] & 0xffff0000u)};
-        if (gelu) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = gelu_tanh_f(v[e]);
-        }
-        const int off = fr * LDW + j * 32 + q * 8 + fh * 4;
-        if (kF32) {
-          *reinterpret_cast<f32x4_t*>(lf + off) = f32x4_t{v[0], v[1], v[2], v[3]};
-        } else {
-          *reinterpret_cast<u32x2_t*>(lds + off) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        }
+        for (int e = 0; e < 4; ++e) v[e] = gelu_tanh_f(v[e]);
       }
+      const int off = pr * LDW + pc;
+      if (kF32) {
+        *reinterpret_cast<f32x4_t*>(lf + off) = f32x4_t{v[0], v[1], v[2], v[3]};
+      } else {
+        *reinterpret_cast<u32x2_t*>(lds + off) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      }
+    }
     if (!kF32) {
 #pragma unroll
       for (int p = 0; p < NPASS; ++p) {
@@ -284,7 +303,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
     _Pragma("unroll") for (int i = 0; i < CB; ++i)                                                     \
       *reinterpret_cast<u32x4_t*>(&sB[buf][(lrow + RSTEP * i) * LDT + kc]) = rb[i];                    \
   } while (0)
-  f32x16_t acc[TM][TN];
+  Acc32<TM, TN> accs;
+  f32x16_t (&acc)[TM][TN] = accs.t;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -322,7 +342,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
 #undef FF_GLOAD
 #undef FF_SSTORE
   // the loop ends with a barrier after every wave's last LDS read
-  epilogue_block<TM, TN, EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, acc, smem + wave * 32 * (WN + 4) * 2);
+  epilogue_block<EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, accs, smem + wave * 32 * (WN + 4) * 2);
 }
 // ------------------------------------------------------------------ bf16 MFMA GEMM, direct-to-LDS
 // For K % BKd == 0 (BKd = 32 or 64).  Operand tiles go global -> LDS with
@@ -374,8 +394,10 @@ __device__ __forceinline__ bf16x8_t lds_rd128(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int BKd, int KG, int AUX, int EPI, bool OUT_F32, bool RES_F32, int NP>
-__global__ __launch_bounds__(KG * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(GemmGroup<NP> G) {
+template <int BM, int BN, int WM, int WN, int NST, int EPI, bool OUT_F32, bool RES_F32, int NP>
+__global__ __launch_bounds__(2 * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(GemmGroup<NP> G) {
+  constexpr int BKd = 64, KG = 2;
+  constexpr int AUX = BN == 64 ? 0 : 17;   // sc0|sc1: skips the L1 (each tile streams its panels once)
   constexpr int NWN = BN / WN;
   constexpr int NW = (BM / WM) * NWN;                            // output blocks (waves per k group)
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -430,7 +452,8 @@ __global__ __launch_bounds__(KG * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(Gem
     }                                                                                                     \
   } while (0)
 
-  f32x16_t acc[TM][TN];
+  Acc32<TM, TN> accs;
+  f32x16_t (&acc)[TM][TN] = accs.t;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -523,133 +546,274 @@ __global__ __launch_bounds__(KG * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(Gem
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][j][v] += red[((i * TN + j) * 16 + v) * 64];
   }
-  epilogue_block<TM, TN, EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, acc, smem + cw * 32 * (WN + 4) * 2);
+  epilogue_block<EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, accs, smem + cw * 32 * (WN + 4) * 2);
 }
 
-// ------------------------------------------------------------------ bf16 MFMA GEMM, 64-wide K stages
-// For K % 64 == 0 on grids that keep the MFMAs busy for a whole stage (see launch_bf16).
-// Two LDS buffers of 64-wide K stages: 128-byte rows (full cache lines per DMA row, 8 rows
-// per 1 KB instruction), XOR swizzle chunk ^ ((row >> 1) & 7).  The DMA of stage kt+1 is issued
-// right after the barrier that ends stage kt-1 (its buffer is free then) and lands during
-// stage kt's four 16-wide k steps, whose fragments are double-buffered in registers as in
-// k_gemm_dl; one wait + barrier per stage.
-template <int BM, int BN, int WM, int WN, int AUX, int EPI, bool OUT_F32, bool RES_F32, int NP>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_dl64(GemmGroup<NP> G) {
-  constexpr int BKd = 64, CH = 8, RPI = 8, KS = 4;
-  constexpr int NWN = BN / WN;
-  constexpr int NW = (BM / WM) * NWN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;
-  static_assert(IA >= 1 && IB >= 1 && TM + TN <= 15, "unsupported tile");
-  constexpr int kMain = 2 * (BM + BN) * BKd, kEpi = epi_lds_elems<NW, WN>();
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kMain > kEpi ? kMain : kEpi];
-  uint16_t (*sA)[BM * BKd] = reinterpret_cast<uint16_t (*)[BM * BKd]>(smem);
-  uint16_t (*sB)[BN * BKd] = reinterpret_cast<uint16_t (*)[BN * BKd]>(smem + 2 * BM * BKd);
-  // wave index in a scalar register: the per-wave LDS addresses of the DMA (M0) are then
-  // computed on the scalar unit instead of with a v_readfirstlane per instruction
+// ------------------------------------------------------------------ bf16 MFMA GEMM, two wave groups in turn
+// 256 x 64 TN tile (TN = 2, 3, 4), 64-wide K stages, 8 waves in two groups of four, one wave
+// of each group per SIMD.  A stage has four phases, one per 32 rows of a wave's 128 x 16 TN
+// block; a phase is a memory part (its fragment reads and two DMA instructions per wave) and
+// 4 TN MFMAs, with a barrier after each.  The second group runs half a phase behind, so that
+// on every SIMD one wave's MFMAs cover the other's reads and DMA.
+//
+// What bounds it: on large grids the card's power limit.  With random operands the clock falls
+// to about 1.7 GHz while the MFMAs are busy 84 % of the cycles, so what counts is energy per
+// FLOP: v_mfma_f32_16x16x32_bf16 moves half the accumulator bytes per FLOP of the 32x32x16
+// form and runs 8 % faster in this same kernel (M = 4608, N = 21504, K = 3072: 496 -> 460 us;
+// one wait and barrier per stage with 32x32x16: 545 us).  On small grids it is bound by its
+// chain of stages: 0.96 us per stage of 256x256 against 0.85 us of MFMA time at 2.4 GHz.
+//
+// Operands: 64-row pieces of 8 KB, each filled by one DMA instruction per wave, in two buffers
+// per operand.  A piece's slot is refilled (two stages ahead) as soon as every wave is past
+// its reads, one phase later, so 8 to 13 of a wave's DMAs stay in flight across every
+// wait, and a piece has at least four phases (2048 cycles at TN = 4) to land.  With both buffers
+// refilled only at stage ends (vmcnt(0) there) the same tile took 545 us on the shape above.
+// Every wave waits for its own LDS reads and for its own share of the pieces that the next
+// phase reads, then for the barrier; the phase that reads a piece starts after that barrier
+// for both groups, and the DMA that overwrites one starts after a barrier that every wave
+// passes with its reads of it complete.
+// Reading one phase ahead (fragments double-buffered) was no faster: 1317 against 1337 TFLOP/s.
+//
+// K % 64 != 0 (K % 8 == 0): the chunks of the last stage past K are loaded from the row's
+// first chunk of that stage (in bounds) and their fragments are zeroed in registers.
+template <int OFF>
+__device__ __forceinline__ bf16x8_t lds_rd128_at(uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
+  u32x4_t v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+// the same with an offset that is a constant once the caller's loop is unrolled
+__device__ __forceinline__ bf16x8_t lds_rd128_off(uint32_t addr, int off) {
+  u32x4_t v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(off) : "memory");
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+template <int V> struct Int { static constexpr int value = V; };
+
+// DMA schedule of k_gemm_pp.  A stage's operands are 4 + TN pieces (A0-A3, B0..).  Phase p of
+// stage k issues, in this order:
+//   0: A3 of stage k+1, A0 of k+2    1: B0, B1 of k+2    2: A1, B2 of k+2    3: A2, B3 of k+2
+// and reads: phase 0 all B of stage k, phases 1-3 A1-A3 of stage k, phase 3 also A0 of k+1.
+// So a piece's slot is refilled no earlier than one phase after its last read, and a piece
+// lands at least four phases after it was issued.
+constexpr int kPPIssue[4][2] = {{3, 0}, {4, 5}, {1, 6}, {2, 7}};   // A0-A3 are 0-3, B0-B3 are 4-7
+// How many of a wave's DMAs may still be outstanding at the end of phase p of a stage with
+// `left` stages after it (2: two or more), so that what phase p + 1 reads has landed.
+constexpr int pp_vm(int TN, int p, int left) {
+  int n = 0, need = -1;   // DMAs issued in stages -2, -1 and 0 (this one) up to phase p; the last one needed
+  for (int j = -2; j <= 0; ++j)
+    for (int q = 0; q < (j == 0 ? p + 1 : 4); ++q)
+      for (int i = 0; i < 2; ++i) {
+        const int pc = kPPIssue[q][i], st = pc == 3 ? j + 1 : j + 2;
+        if (pc >= 4 + TN || st > left) continue;
+        ++n;
+        const bool next = (p == 0 && pc == 1 && st == 0) || (p == 1 && pc == 2 && st == 0) ||
+                          (p == 2 && ((pc == 3 && st == 0) || (pc == 0 && st == 1))) || (p == 3 && pc >= 4 && st == 1);
+        if (next) need = n;
+      }
+  return need < 0 ? 63 : n - need;
+}
+
+#define FF_RDA(dst, off)                                             \
+  do {                                                               \
+    (dst)[0] = lds_rd128_at<(off)>(rda[0]);                          \
+    (dst)[1] = lds_rd128_at<(off)>(rda[1]);                          \
+    (dst)[2] = lds_rd128_at<(off) + 16 * 128>(rda[0]);               \
+    (dst)[3] = lds_rd128_at<(off) + 16 * 128>(rda[1]);               \
+  } while (0)
+#define FF_TIE(x) asm volatile("" : "+v"(x))
+
+template <int TN, int EPI, bool OUT_F32, bool RES_F32, int NP>
+__global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the launch stub only
+  constexpr int BM = 256, BN = 64 * TN, WN = 16 * TN, BKd = 64, RB = 128;   // RB: bytes of an LDS row
+  constexpr int PC = 64 * RB;                                                // bytes of a piece
+  constexpr int BUFA = 4 * PC, BUFB = TN * PC, OFFB = 2 * BUFA;
+  constexpr int kMain = OFFB + 2 * BUFB, kEpi = epi_lds_elems<8, WN>() * 2;
+  __shared__ __attribute__((aligned(1024))) uint16_t smem[(kMain > kEpi ? kMain : kEpi) / 2];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tm, tn;
-  // workgroup-uniform: keep the problem select and tile origin in scalar registers
   const int prob = __builtin_amdgcn_readfirstlane(tile_of(blockIdx.x, G.tm[0], G.tn[0], G.tm[NP - 1], G.tn[NP - 1], NP, tm, tn));
   tm = __builtin_amdgcn_readfirstlane(tm);
   tn = __builtin_amdgcn_readfirstlane(tn);
   const GemmArgs a = (NP > 1 && prob) ? G.g[NP - 1] : G.g[0];
   const int m0 = tm * BM, n0 = tn * BN;
-  const uint16_t* A = reinterpret_cast<const uint16_t*>(a.A);
-  const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
-  const int lr = lane / CH, ls = lane % CH;
-  // Only waves 0..NW/2-1 issue the DMA, each for its own rows and those of wave + NW/2 (one
-  // issuing wave per SIMD).  A stage's DMA goes out as a burst that can fill the L1's
-  // outstanding-request queue; a wave stalled issuing it cannot issue its MFMAs either,
-  // and with half the waves free of DMA every SIMD keeps a wave that can (DiT-XL/2 fc1
-  // 35.0 -> 32.8 us, FLUX-like qkv, proj, fc2 and lin2 3-7 % faster).
-  constexpr int HW = NW / 2;
-  static_assert(NW % 2 == 0, "issuing waves pair with the upper half");
-  size_t ga[2 * IA], gb[2 * IB];
-  int wa[2 * IA], wb[2 * IB];
+  const int mw = wave >> 2, nw = wave & 3;
+  const int nk = (a.K + BKd - 1) / BKd, kpad = nk * BKd - a.K;
+  // operand bases of this tile (scalar) and per-lane byte offsets of its DMA rows: a piece is
+  // 64 LDS rows, 8 per wave and instruction.  Piece Aq holds rows 32 q .. 32 q + 31 of both
+  // wave rows, piece Bu columns 16 u .. 16 u + 15 of all four wave columns.  Rows past the
+  // matrix read the tile's first row (in bounds); their results are never stored.
+  const int p0 = a.amap.phys(m0);
+  const char* Ab = reinterpret_cast<const char*>(a.A) + (size_t)p0 * a.lda * 2;
+  const char* Wb = reinterpret_cast<const char*>(a.W) + (size_t)n0 * a.ldw * 2;
+  __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Ab), 0, 0xffffffffu, 0x00020000);
+  __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Wb), 0, 0xffffffffu, 0x00020000);
+  const int R = wave * 8 + (lane >> 3);
+  const uint32_t ch = ((lane & 7) ^ ((R >> 1) & 7)) * 16;
+  uint32_t voa[4], vob[TN];
 #pragma unroll
-  for (int j = 0; j < 2 * IA; ++j) {
-    const int w = j < IA ? wave : wave + HW, jj = j % IA;
-    wa[j] = (w * IA + jj) * RPI * BKd;
-    const int row = (w * IA + jj) * RPI + lr, gm = m0 + row;
-    ga[j] = (size_t)a.amap.phys(gm < a.M ? gm : 0) * a.lda + ((ls ^ ((row >> 1) & 7)) * 8);
+  for (int q = 0; q < 4; ++q) {
+    const int gm = m0 + (R >> 5) * 128 + q * 32 + (R & 31);
+    voa[q] = (gm < a.M ? (uint32_t)(a.amap.phys(gm) - p0) * (uint32_t)a.lda * 2u : 0u) + ch;
   }
 #pragma unroll
-  for (int j = 0; j < 2 * IB; ++j) {
-    const int w = j < IB ? wave : wave + HW, jj = j % IB;
-    wb[j] = (w * IB + jj) * RPI * BKd;
-    const int row = (w * IB + jj) * RPI + lr, gn = n0 + row;
-    gb[j] = (size_t)(gn < a.N ? gn : 0) * a.ldw + ((ls ^ ((row >> 1) & 7)) * 8);
+  for (int u = 0; u < TN; ++u) {
+    const int gn = (R >> 4) * WN + u * 16 + (R & 15);
+    vob[u] = (n0 + gn < a.N ? (uint32_t)gn * (uint32_t)a.ldw * 2u : 0u) + ch;
   }
-#define FF_ISSUE(st, k0)                                                                                  \
-  do {                                                                                                    \
-    if (wave < HW) {                                                                                      \
-    _Pragma("unroll") for (int j = 0; j < 2 * IA; ++j)                                                    \
-      __builtin_amdgcn_global_load_lds(FF_AS1(A + ga[j] + (k0)), FF_AS3(&sA[st][wa[j]]), 16, 0, AUX); \
-    _Pragma("unroll") for (int j = 0; j < 2 * IB; ++j)                                                    \
-      __builtin_amdgcn_global_load_lds(FF_AS1(W + gb[j] + (k0)), FF_AS3(&sB[st][wb[j]]), 16, 0, AUX); \
-    }                                                                                                     \
+  // K % 64 != 0: the last stage's chunks past K load the row's chunk 0 of that stage instead
+  // (in bounds), and their fragments are zeroed
+  const uint32_t back = (kpad && ch >= (uint32_t)(BKd - kpad) * 2u) ? ch : 0u;
+  char* const lds = reinterpret_cast<char*>(smem);
+#define FF_DMA(rs, vo, dst, kb) __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, FF_AS3(lds + (dst) + wave * 1024), 16, vo, kb, 0, 0)
+  Acc16<8, TN> accs;
+  f32x4_t (&acc)[8][TN] = accs.t;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fh = lane >> 4;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)smem);
+  uint32_t rda[2], rdb[2];   // fragment addresses of the two 32-wide k steps, current buffers
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const uint32_t c = ((4 * s + fh) ^ (fr >> 1)) * 16;
+    rda[s] = lds0 + (mw * 32 + fr) * RB + c;
+    rdb[s] = lds0 + OFFB + (nw * 16 + fr) * RB + c;
+  }
+  bf16x8_t fa[2][4], fb[2 * TN];
+  int kb = 0, ca = 0, cb = 0;   // this stage's byte offset along K, and its buffers
+#define FF_MEM_END() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
+#define FF_MMA(q, A)                                                                                            \
+  do {                                                                                                          \
+    __builtin_amdgcn_sched_barrier(0);                                                                          \
+    __builtin_amdgcn_s_setprio(1);                                                                              \
+    _Pragma("unroll") for (int s = 0; s < 2; ++s)                                                               \
+      _Pragma("unroll") for (int t = 0; t < 2; ++t)                                                             \
+        _Pragma("unroll") for (int u = 0; u < TN; ++u)                                                          \
+          acc[2 * (q) + t][u] =                                                                                 \
+              __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[2 * u + s], (A)[2 * t + s], acc[2 * (q) + t][u], 0, 0, 0); \
+    __builtin_amdgcn_s_setprio(0);                                                                              \
+    __builtin_amdgcn_sched_barrier(0);                                                                          \
+    asm volatile("s_barrier" ::: "memory");                                                                     \
   } while (0)
-  f32x16_t acc[TM][TN];
+#define FF_TIEA(A) _Pragma("unroll") for (int i = 0; i < 4; ++i) FF_TIE((A)[i])
+  // zero the fragments whose k lies past K (last stage; both operands, so that 0 * 0 is added)
+  auto cut = [&](bf16x8_t& f, int s) __attribute__((always_inline)) {
+    u32x4_t w = __builtin_bit_cast(u32x4_t, f);
+    const bool in = (4 * s + fh) * 8 < BKd - kpad;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int wm = (wave / NWN) * WM, wn = (wave % NWN) * WN;
-  const int fr = lane & 31, fh = lane >> 5;
-  int rowa[TM], rowb[TN];
-#pragma unroll
-  for (int t = 0; t < TM; ++t) rowa[t] = wm + t * 32 + fr;
-#pragma unroll
-  for (int t = 0; t < TN; ++t) rowb[t] = wn + t * 32 + fr;
-  const int nk = a.K / BKd;
-  FF_ISSUE(0, 0);
-  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-  bf16x8_t fa[2][TM], fb[2][TN];
-  for (int kt = 0; kt < nk; ++kt) {
-    const int st = kt & 1;
-    if (kt + 1 < nk) FF_ISSUE(st ^ 1, (kt + 1) * BKd);   // buffer of stage kt-1: free after the last barrier
-#pragma unroll
-    for (int t = 0; t < TM; ++t) fa[0][t] = lds_rd128(&sA[st][rowa[t] * BKd + ((fh ^ ((rowa[t] >> 1) & 7)) * 8)]);
-#pragma unroll
-    for (int t = 0; t < TN; ++t) fb[0][t] = lds_rd128(&sB[st][rowb[t] * BKd + ((fh ^ ((rowb[t] >> 1) & 7)) * 8)]);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      const int cur = s & 1, nxt = cur ^ 1;
-      if (s + 1 < KS) {
-        const int ch = (s + 1) * 2 + fh;
-#pragma unroll
-        for (int t = 0; t < TM; ++t) fa[nxt][t] = lds_rd128(&sA[st][rowa[t] * BKd + ((ch ^ ((rowa[t] >> 1) & 7)) * 8)]);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) fb[nxt][t] = lds_rd128(&sB[st][rowb[t] * BKd + ((ch ^ ((rowb[t] >> 1) & 7)) * 8)]);
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(TM + TN) : "memory");
-      } else {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      }
-#pragma unroll
-      for (int t = 0; t < TM; ++t) asm volatile("" : "+v"(fa[cur][t]));
-#pragma unroll
-      for (int t = 0; t < TN; ++t) asm volatile("" : "+v"(fb[cur][t]));
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-    }
-    // stage kt+1 landed everywhere, and every wave is done reading stage kt.  The
-    // scheduling fence keeps every MFMA of this stage above the wait: the compiler would
-    // otherwise sink them below the barrier (they touch no memory), which delays the next
-    // stage's DMA by their issue time and idles the matrix cores during the wait
-    // (FLUX-like qkv 293 -> 264 us, DiT-XL/2 fc1 39.3 -> 36.4 us)
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int e = 0; e < 4; ++e) w[e] = in ? w[e] : 0u;
+    f = __builtin_bit_cast(bf16x8_t, w);
+  };
+#define FF_CUTA(A)                                          \
+  if (LEFT == 0 && kpad) {                                  \
+    _Pragma("unroll") for (int i = 0; i < 4; ++i) cut((A)[i], i & 1); \
   }
-#undef FF_ISSUE
-  // the loop ends with a barrier after every wave's last LDS read
-  epilogue_block<TM, TN, EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, acc, smem + wave * 32 * (WN + 4) * 2);
+  // one stage.  LEFT: stages after it (2: two or more)
+  auto stage = [&](auto LEFTc) __attribute__((always_inline)) {
+    constexpr int LEFT = decltype(LEFTc)::value;
+    constexpr bool k1 = LEFT >= 1, k2 = LEFT >= 2;
+    const int oa = BUFA - ca, ob = BUFB - cb;
+    // phase 0
+#pragma unroll
+    for (int u = 0; u < TN; ++u) {
+      fb[2 * u] = lds_rd128_off(rdb[0], u * PC);
+      fb[2 * u + 1] = lds_rd128_off(rdb[1], u * PC);
+    }
+    if (k1) FF_DMA(ra, voa[3], 3 * PC + oa, kb + RB);
+    if (k2) FF_DMA(ra, voa[0], ca, kb + 2 * RB);
+    wait_vm<pp_vm(TN, 0, LEFT)>();
+    FF_MEM_END();
+#pragma unroll
+    for (int i = 0; i < 2 * TN; ++i) FF_TIE(fb[i]);
+    if (LEFT == 0 && kpad) {
+#pragma unroll
+      for (int i = 0; i < 2 * TN; ++i) cut(fb[i], i & 1);
+    }
+    FF_CUTA(fa[0]);
+    FF_MMA(0, fa[0]);
+    // phase 1
+    FF_RDA(fa[1], 1 * PC);
+    if (k2) {
+      FF_DMA(rw, vob[0], OFFB + cb, kb + 2 * RB);
+      FF_DMA(rw, vob[1], OFFB + PC + cb, kb + 2 * RB);
+    }
+    wait_vm<pp_vm(TN, 1, LEFT)>();
+    FF_MEM_END();
+    FF_TIEA(fa[1]);
+    FF_CUTA(fa[1]);
+    FF_MMA(1, fa[1]);
+    // phase 2
+    FF_RDA(fa[0], 2 * PC);
+    if (k2) {
+      FF_DMA(ra, voa[1], PC + ca, kb + 2 * RB);
+      if (TN > 2) FF_DMA(rw, vob[TN > 2 ? 2 : 0], OFFB + 2 * PC + cb, kb + 2 * RB);
+    }
+    wait_vm<pp_vm(TN, 2, LEFT)>();
+    FF_MEM_END();
+    FF_TIEA(fa[0]);
+    FF_CUTA(fa[0]);
+    FF_MMA(2, fa[0]);
+    // phase 3
+    FF_RDA(fa[1], 3 * PC);
+    rda[0] += oa - ca; rda[1] += oa - ca;
+    rdb[0] += ob - cb; rdb[1] += ob - cb;
+    if (k1) FF_RDA(fa[0], 0);
+    if (k2) {
+      FF_DMA(ra, voa[2], 2 * PC + ca, kb + 2 * RB);
+      if (TN > 3) FF_DMA(rw, vob[TN > 3 ? 3 : 0], OFFB + 3 * PC + cb, kb + 2 * RB);
+    }
+    wait_vm<pp_vm(TN, 3, LEFT)>();
+    FF_MEM_END();
+    FF_TIEA(fa[1]);
+    if (k1) { FF_TIEA(fa[0]); }
+    FF_CUTA(fa[1]);
+    FF_MMA(3, fa[1]);
+    kb += RB;
+    ca = oa;
+    cb = ob;
+  };
+  // prologue: what the stages -2 and -1 would have issued, in that order
+#pragma unroll
+  for (int j = -2; j < 0; ++j)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int pc = kPPIssue[q / 2][q % 2], st = pc == 3 ? j + 1 : j + 2;
+      if (pc >= 4 + TN || st < 0) continue;
+      if (pc < 4) FF_DMA(ra, voa[pc & 3], st * BUFA + pc * PC, st * RB);
+      else FF_DMA(rw, vob[pc - 4 < TN ? pc - 4 : 0], OFFB + st * BUFB + (pc - 4) * PC, st * RB);
+    }
+  wait_vm<3 + TN>();   // stage 0 has landed, and stage 1 but for A3 is on its way
+  asm volatile("s_barrier" ::: "memory");
+  if (wave >= 4) asm volatile("s_barrier" ::: "memory");   // the second group runs half a phase behind
+  FF_RDA(fa[0], 0);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  FF_TIEA(fa[0]);
+  for (int kt = 0; kt < nk - 3; ++kt) stage(Int<2>{});
+  // the pieces issued from here on are the last stage's, but for A3 of the last but one
+#pragma unroll
+  for (int q = 0; q < 3; ++q) voa[q] -= back;
+#pragma unroll
+  for (int u = 0; u < TN; ++u) vob[u] -= back;
+  stage(Int<2>{});
+  voa[3] -= back;
+  stage(Int<1>{});
+  stage(Int<0>{});
+  if (wave < 4) asm volatile("s_barrier" ::: "memory");
+#undef FF_TIEA
+#undef FF_CUTA
+#undef FF_MEM_END
+#undef FF_DMA
+#undef FF_MMA
+  // every wave's LDS reads and DMA ended before the last barrier
+  epilogue_block<EPI, OUT_F32, RES_F32>(a, m0 + mw * 128, n0 + nw * WN, accs, smem + wave * 32 * (WN + 4) * 2);
+#endif
 }
-
 
 // ------------------------------------------------------------------ fp32 FMA GEMM
 template <int EPI>
@@ -721,67 +885,54 @@ void launch_tile(const GemmArgs* a, int n, hipStream_t s) {
   }
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int BKd, int KG, int AUX, int EPI, bool OF, bool RF>
+template <int BM, int BN, int WM, int WN, int NST, int EPI, bool OF, bool RF>
 void launch_dl(const GemmArgs* a, int n, hipStream_t s) {
   int nwg;
   if (n == 1) {
     const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, BKd, KG, AUX, EPI, OF, RF, 1>), nwg, KG * (BM / WM) * (BN / WN) * 64, 0, s, G);
+    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, EPI, OF, RF, 1>), nwg, 2 * (BM / WM) * (BN / WN) * 64, 0, s, G);
   } else {
     const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, BKd, KG, AUX, EPI, OF, RF, 2>), nwg, KG * (BM / WM) * (BN / WN) * 64, 0, s, G);
+    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, EPI, OF, RF, 2>), nwg, 2 * (BM / WM) * (BN / WN) * 64, 0, s, G);
   }
 }
 
-template <int BM, int BN, int WM, int WN, int AUX, int EPI, bool OF, bool RF>
-void launch_dl64(const GemmArgs* a, int n, hipStream_t s) {
+template <int TN, int EPI, bool OF, bool RF>
+void launch_pp(const GemmArgs* a, int n, hipStream_t s) {
   int nwg;
   if (n == 1) {
-    const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_dl64<BM, BN, WM, WN, AUX, EPI, OF, RF, 1>), nwg, (BM / WM) * (BN / WN) * 64, 0, s, G);
+    const GemmGroup<1> G = make_group<256, 64 * TN, 1>(a, nwg);
+    FF_LAUNCH((k_gemm_pp<TN, EPI, OF, RF, 1>), nwg, 512, 0, s, G);
   } else {
-    const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_dl64<BM, BN, WM, WN, AUX, EPI, OF, RF, 2>), nwg, (BM / WM) * (BN / WN) * 64, 0, s, G);
+    const GemmGroup<2> G = make_group<256, 64 * TN, 2>(a, nwg);
+    FF_LAUNCH((k_gemm_pp<TN, EPI, OF, RF, 2>), nwg, 512, 0, s, G);
   }
 }
 
-// Tile choice for K % 64 == 0: the candidate minimising (rounds of workgroups over the
-// 256 CUs) x (time of one round of that candidate), measured on MI355X with random bf16
-// data and expressed relative to a round of 256x256 tiles (the ratio drifts with K, e.g.
-// 0.36 at K = 1152 and 0.29 at K = 4608 for 128x96; the constants sit between).
-//   kTile256     256x256, 8 waves of 128x64, 2 x 64-wide stages, 1 per CU          1.00
-//   kTile256x192 256x192, 8 waves of 64x96,  2 x 64-wide stages, 1 per CU          0.91
-//   kTile128x2   128x128, 8 waves of 64x32, 2 x 64-wide stages, 2 per CU (512/round) 0.80
-//   kTile128     128x128, 4 blocks of 64x64 x 2 k groups, 4 x 64-wide stages        0.41
-//   kTile128x96  128x96,  4 blocks of 32x96 x 2 k groups, 4 x 64-wide stages        0.34
-//   kTile128x64  128x64,  4 blocks of 32x64 x 2 k groups, 4 x 64-wide stages        0.24
-// Larger tiles need fewer operand bytes per MFMA (LDS traffic per MFMA limits the 128x128
-// tiles), smaller ones fill the CUs on small grids (M = 2048 shapes).  The 128-row ring
-// tiles run two k groups of waves per output block (8 waves, two per SIMD): one wave's
-// LDS reads and barrier waits then overlap the other's MFMAs.  Operands of the 256-row
-// tiles load with sc0|sc1 (they skip the L1; each tile streams its panels once).
-// A group is costed by its total tile count.  K % 32 == 0 only: 4 x 32-wide stages,
-// 256x256 from 160 such tiles on, else 128x128; otherwise the register-staged kernel.
-enum { kTile256, kTile256x192, kTile128x2, kTile128, kTile128x96, kTile128x64, kTileCount };
+// Tile choice: the candidate with the least estimated time.  A candidate's round of
+// workgroups over the 256 CUs takes lat + k * K us when it is bound by its own chain of
+// stages, and its tiles keep the whole card busy for pow us per 256 tiles and unit of K when
+// the card's power limit binds (large grids: the clock falls to about 1.6 GHz, so that a
+// grid that leaves CUs idle runs its tiles faster).  Measured on MI355X with random bf16
+// data; 256 x 64 TN tiles run k_gemm_pp, 128-row tiles k_gemm_dl.  In us at K = 1152 / 4608 /
+// 15360 for one round of few tiles: 256x256 31 / 85 / 230, 256x192 28 / 70 / 188, 256x128
+// 21 / 57 / 159, 128x96 15 / 37 / -, 128x64 10 / 29 / -; a full round at K = 3072 (clock
+// down): 77, 62, 47 us.  What the choice picks, against the kernels this replaced (256x256 and
+// 256x192 of 32x32x16 MFMAs with one wait and barrier per stage, 128x128 two per CU): M = 4608,
+// N = 21504, K = 3072 545 -> 460 us (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us,
+// 14310 x 8192 x 2048 440 -> 370 us, 8192 x 4608 x 1152 100 -> 89 us, 2048 x 3456 x 1152
+// 26.1 -> 20.8 us.
+enum { kTile256, kTile256x192, kTile256x128, kTile128, kTile128x96, kTile128x64, kTileCount };
 struct TilePlan { int tile; double cost; };
+struct TileCost { int bm, bn; double lat, k, pow; };
+constexpr TileCost kTileCost[kTileCount] = {
+    {256, 256, 15.0, 0.0150, 0.0245}, {256, 192, 13.0, 0.0122, 0.0192}, {256, 128, 9.0, 0.0103, 0.0145},
+    {128, 128, 9.5, 0.0076, 0.0145},  {128, 96, 8.3, 0.0062, 0.0120},   {128, 64, 4.2, 0.0054, 0.0100}};
 
 long tiles_of(const GemmArgs* a, int n, int bm, int bn) {
   long t = 0;
   for (int i = 0; i < n; ++i) t += (long)((a[i].M + bm - 1) / bm) * ((a[i].N + bn - 1) / bn);
   return t;
-}
-
-TilePlan plan_k64(const GemmArgs* a, int n) {
-  static const double kRound[kTileCount] = {1.00, 0.91, 0.80, 0.41, 0.34, 0.24};
-  const long t[kTileCount] = {tiles_of(a, n, 256, 256), tiles_of(a, n, 256, 192), tiles_of(a, n, 128, 128),
-                              tiles_of(a, n, 128, 128), tiles_of(a, n, 128, 96), tiles_of(a, n, 128, 64)};
-  const long per_round[kTileCount] = {256, 256, 512, 256, 256, 256};
-  TilePlan best{kTile256, 1e300};
-  for (int c = 0; c < kTileCount; ++c) {
-    const double cost = (double)((t[c] + per_round[c] - 1) / per_round[c]) * kRound[c];
-    if (cost < best.cost) best = TilePlan{c, cost};
-  }
-  return best;
 }
 
 bool all_k(const GemmArgs* a, int n, int m) {
@@ -790,22 +941,43 @@ bool all_k(const GemmArgs* a, int n, int m) {
   return true;
 }
 
+// k_gemm_pp takes three or more 64-wide stages, and its operand rows lie within a 32-bit byte
+// offset of their tile's first row (256 consecutive rows of a row map span at most
+// 255 / n_seg + 1 further samples).
+bool pp_ok(const GemmArgs* a, int n) {
+  for (int i = 0; i < n; ++i) {
+    const RowMap& m = a[i].amap;
+    const uint64_t span = m.n_seg == m.N ? 256 : (uint64_t)(255 / m.n_seg + 1) * m.N + 256;
+    if (a[i].K <= 128 || span * a[i].lda * 2 > 0xf0000000ull || 256ull * a[i].ldw * 2 > 0xf0000000ull) return false;
+  }
+  return true;
+}
+
+TilePlan plan_tiles(const GemmArgs* a, int n) {
+  const bool pp = pp_ok(a, n), ring = all_k(a, n, 64);
+  int K = 0;
+  for (int i = 0; i < n; ++i) K = std::max(K, a[i].K);
+  TilePlan best{-1, 1e300};
+  for (int c = 0; c < kTileCount; ++c) {
+    if (c < kTile128 ? !pp : !ring) continue;
+    const TileCost& t = kTileCost[c];
+    const long tiles = tiles_of(a, n, t.bm, t.bn);
+    const double cost = std::max((double)((tiles + 255) / 256) * (t.lat + t.k * K), tiles / 256.0 * t.pow * K);
+    if (cost < best.cost) best = TilePlan{c, cost};
+  }
+  return best;
+}
+
 template <int EPI, bool OF, bool RF>
 void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
-  if (!all_k(a, n, 32)) {
-    launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s);
-  } else if (!all_k(a, n, 64)) {
-    if (tiles_of(a, n, 256, 256) >= 160) launch_dl<256, 256, 128, 64, 4, 32, 1, 17, EPI, OF, RF>(a, n, s);
-    else launch_dl<128, 128, 64, 32, 4, 32, 1, 0, EPI, OF, RF>(a, n, s);
-  } else {
-    switch (plan_k64(a, n).tile) {
-      case kTile256: launch_dl64<256, 256, 128, 64, 17, EPI, OF, RF>(a, n, s); break;
-      case kTile256x192: launch_dl64<256, 192, 64, 96, 17, EPI, OF, RF>(a, n, s); break;
-      case kTile128x2: launch_dl64<128, 128, 64, 32, 0, EPI, OF, RF>(a, n, s); break;
-      case kTile128: launch_dl<128, 128, 64, 64, 4, 64, 2, 17, EPI, OF, RF>(a, n, s); break;
-      case kTile128x96: launch_dl<128, 96, 32, 96, 4, 64, 2, 17, EPI, OF, RF>(a, n, s); break;
-      default: launch_dl<128, 64, 32, 64, 4, 64, 2, 0, EPI, OF, RF>(a, n, s); break;
-    }
+  switch (plan_tiles(a, n).tile) {
+    case kTile256: launch_pp<4, EPI, OF, RF>(a, n, s); break;
+    case kTile256x192: launch_pp<3, EPI, OF, RF>(a, n, s); break;
+    case kTile256x128: launch_pp<2, EPI, OF, RF>(a, n, s); break;
+    case kTile128: launch_dl<128, 128, 64, 64, 4, EPI, OF, RF>(a, n, s); break;
+    case kTile128x96: launch_dl<128, 96, 32, 96, 4, EPI, OF, RF>(a, n, s); break;
+    case kTile128x64: launch_dl<128, 64, 32, 64, 4, EPI, OF, RF>(a, n, s); break;
+    default: launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s); break;   // K <= 128 off the 64 grid
   }
 }
 
@@ -860,17 +1032,10 @@ hipError_t gemm2(int dtype, const GemmArgs& a0, const GemmArgs& a1, hipStream_t 
   const bool e0 = a0.M > 0 && a0.N > 0, e1 = a1.M > 0 && a1.N > 0;
   const bool ungated = a0.epi != EPI_GATED && a1.epi != EPI_GATED;
   const bool same = (a0.epi == a1.epi || ungated) && a0.out_f32 == a1.out_f32 && a0.resid_f32 == a1.resid_f32;
-  // Grouping pays when the combined launch costs no more rounds than the two launches
-  // (same cost model as the tile choice; with K % 64 != 0, by 256x256 rounds).
+  // Grouping pays when the combined launch is estimated to take no longer than the two.
   const GemmArgs both[2] = {a0, a1};
-  bool pays;
-  if (all_k(both, 2, 64)) {
-    pays = plan_k64(both, 2).cost <= plan_k64(&a0, 1).cost + plan_k64(&a1, 1).cost;
-  } else {
-    const long t0 = tiles_of(&a0, 1, 256, 256), t1 = tiles_of(&a1, 1, 256, 256);
-    const long rg = (t0 + t1 + 255) / 256, r0 = (t0 + 255) / 256, r1 = (t1 + 255) / 256;
-    pays = t0 + t1 < 160 || rg <= (r0 > r1 ? r0 : r1) || ((t0 < t1 ? t0 : t1) >= 160 && rg < r0 + r1);
-  }
+  const TilePlan pb = plan_tiles(both, 2);
+  const bool pays = pb.tile < 0 || pb.cost <= plan_tiles(&a0, 1).cost + plan_tiles(&a1, 1).cost;
   if (dtype == DT_F32 || !same || !e0 || !e1 || !pays) {
     hipError_t e = gemm(dtype, a0, s);
     return e != hipSuccess ? e : gemm(dtype, a1, s);

@@ -222,3 +222,20 @@ def test_flux_block_rope_full_shape_sampled_rows(kind):
     W = synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1)
     say(f"flux rope full block kind={kind} (sampled rows)")
     check_block(cfg, W, rows=np.array(SAMPLE_ROWS["flux"]))
+
+
+@pytest.mark.parametrize("kind,H,B,lat,n_txt", [
+    (synth.DIT, 33, 32, (4, 1, 28, 64), 0),            # K = 264 / 528, M = 14336: 256x256 tiles
+    (synth.DIT, 33, 20, (4, 1, 32, 64), 0),            # M = 10240: 256x192 tiles
+    (synth.DIT, 23, 3, (4, 1, 26, 44), 0),             # K = 184 (three stages) / 368, M = 858: 256x128 tiles, row tail
+    (synth.DIT, 31, 1, (4, 1, 6, 10), 0),              # K = 248 / 496, M = 15: one short row tile
+    (synth.MMDIT_DOUBLE, 25, 3, (4, 1, 18, 22), 13),   # K = 200 / 400, text rows of three samples in one tile
+    (synth.MMDIT_SINGLE, 35, 2, (4, 1, 20, 30), 21),   # K = 280 / 840: odd and even stage counts
+])
+def test_block_gemm_tiles_off_the_64_grid(kind, H, B, lat, n_txt):
+    """K not a multiple of 64 takes the 256-row GEMM tiles at every grid size (three stages
+    and more, a partial last stage, row and column tails, rows through a row map)."""
+    need_gpu()
+    cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
+    check_block(cfg, W, seed=H)
