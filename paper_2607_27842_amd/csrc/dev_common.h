@@ -128,4 +128,52 @@ __device__ __forceinline__ float wave_max(float v) {
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
+// ---------------------------------------------------------------- LDS reads and DMA by hand
+// Kernels that keep global -> LDS DMA in flight across their LDS reads issue both by hand:
+// the compiler would wait for all DMA before a read that may alias it.  A fragment read
+// here is complete after an s_waitcnt lgkmcnt that covers it and must then pass FF_TIE
+// before its first use, in the same straight-line code, so that no use or copy moves above
+// the wait.
+#define FF_AS1(p) ((const __attribute__((address_space(1))) void*)(p))
+#define FF_AS3(p) ((__attribute__((address_space(3))) void*)(p))
+#define FF_TIE(x) asm volatile("" : "+v"(x))
+
+__device__ __forceinline__ bf16x8_t lds_rd128(const uint16_t* p) {
+  u32x4_t v;
+  const uint32_t off = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)p);
+  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(off) : "memory");
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8_t lds_rd128_at(uint32_t addr) {
+  static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
+  u32x4_t v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+// the same with an offset that is a constant once the caller's loop is unrolled
+__device__ __forceinline__ bf16x8_t lds_rd128_off(uint32_t addr, int off) {
+  u32x4_t v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(off) : "memory");
+  return __builtin_bit_cast(bf16x8_t, v);
+}
+// 4 rows x 16 columns of 16-bit elements per 16 lanes, transposed: lane i of the 16 addresses
+// row i / 4, columns 4 (i % 4) .. + 3 and gets column i, rows 0-3
+__device__ __forceinline__ u32x2_t lds_rd64_tr(uint32_t addr, int off) {
+  u32x2_t v;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(off) : "memory");
+  return v;
+}
+template <int N>
+__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+template <int V> struct Int { static constexpr int value = V; };
+// f(Int<I>) for I = A .. B - 1
+template <int A, int B, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (A < B) {
+    f(Int<A>{});
+    static_for<A + 1, B>(f);
+  }
+}
+
 }  // namespace ff

@@ -2,11 +2,10 @@
 // tiles are staged through LDS and each wavefront keeps a running (max, sum) per query
 // (online softmax), so no N x N matrix is ever stored.
 //
-// bf16: v_mfma_f32_32x32x16_bf16 (the full-rate gfx950 bf16 MFMA).  A wavefront owns 32
-// queries; a workgroup of 4 or 8 wavefronts shares each 64-key tile.  Scores are formed
-// transposed, S^T = K Q^T, so every lane holds the scores of ONE query: the softmax
-// statistics are lane-local plus one cross-lane step, and the probabilities are already
-// in the register layout of the B operand of O^T = V^T P^T (no shuffle).
+// bf16: v_mfma_f32_16x16x32_bf16.  A wavefront owns 16 or 32 queries; the 8 wavefronts of a
+// workgroup share each 64-key tile.  Scores are formed transposed, S^T = K Q^T, so every
+// lane holds scores of ONE query (per 16-query tile), and the probabilities are already in the
+// register layout of the B operand of O^T = V^T P^T (no shuffle).
 // fp32: one thread per query, 32-key LDS tiles (small fp32 workloads only).
 #include "dev_common.h"
 
@@ -14,339 +13,302 @@ namespace ff {
 
 namespace {
 
-constexpr int KT = 64;  // keys per LDS tile
-constexpr float kLazy = 8.0f;  // log2 headroom before the running max is raised
+constexpr float kPLim = 256.0f;   // a lane's probability sum per query and tile that raises the running max
 
-// ---------------------------------------------------------------- bf16, 32x32x16 MFMA
-// NW wavefronts x 32 queries per workgroup; 64-key K/V tiles staged through LDS (K row-
-// major, V transposed), the next tile prefetched into registers during the current one.
-// v_mfma_f32_32x32x16_bf16 layouts (A lane l: row l%32, k 8*(l/32)+0..7; B lane l: col
-// l%32, same k; D[v] at row 8*(v/4) + 4*(l/32) + v%4, col l%32):
-//   S^T = K Q^T : A = K (32 keys x 16 dims), B = Q^T (16 dims x 32 queries) -> lane l holds
-//                 16 scores of query l%32, keys 8*(v/4) + 4*(l/32) + v%4 of a 32-key tile.
-//   O^T += V^T P^T : B = P^T needs, per lane, the probabilities of query l%32 at 8 keys
-//                 for the MFMA k index 8*(l/32)+j; mapping k index j to key
-//                 (j<4 ? 4h+j : 8+4h+j-4) (+16 for the second half of the tile) makes that
-//                 exactly the registers the lane already holds.  A = V^T rows (e) at those
-//                 keys; the transposed V tile stores key k of each 16-key group at column
-//                 vpos(k) (bits 2 and 3 swapped), which makes them one 16-byte LDS read.
-// Head dims are zero-padded: QK^T to a multiple of 16 (DQ), PV to a multiple of 32 (DV).
-__device__ __forceinline__ int vpos(int k) { return (k & ~12) | ((k & 4) << 1) | ((k & 8) >> 1); }
-
-// The two halves of a wavefront exchanged in registers (v_permlane32_swap, no LDS round
-// trip): every lane gets lo = x of lane l % 32 and hi = x of lane l % 32 + 32, so a
-// combination of lo and hi is the same value in lanes l and l ^ 32.
-__device__ __forceinline__ void wave_halves(float x, float& lo, float& hi) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  lo = __uint_as_float(r[0]);
-  hi = __uint_as_float(r[1]);
-}
-
-template <int DQ, int DV, int NW, int SPLIT, int KTL>   // KTL: keys per LDS tile (64 or 128)
-__global__ __launch_bounds__(NW * SPLIT * 64) void k_attn32(AttnArgs a) {
-  constexpr int NS = KTL / 32;        // 32-key score tiles per LDS tile
-  constexpr int NT = NW * 64;   // threads of one group
-  constexpr int LDK = DQ + 8;         // K tile row stride (elements)
-  constexpr int LDV = KTL + 8;        // V^T tile row stride
-  constexpr int NQC = DQ / 16;        // 16-wide head-dim chunks of QK^T
-  constexpr int NOT = DV / 32;        // 32-wide output tiles of the head dim
-  constexpr int KCH = KTL * (DQ / 8); // 16-byte chunks of a K tile
-  constexpr int PK = (KCH + NT - 1) / NT;
-  constexpr int VG = (KTL / 4) * (DV / 8);  // V groups: 4 consecutive keys x 8 head dims
-  constexpr int PV = (VG + NT - 1) / NT;
-  static_assert(DV <= DQ + 16, "layout");
-  // per group: two K tiles [KTL][LDK] and two V^T tiles [DV][LDV]
-  constexpr int KSZ = KTL * LDK, VSZ = DV * LDV;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[SPLIT * 2 * (KSZ + VSZ)];
-  auto Ks = [&](int g, int b) { return smem + (g * 2 + b) * KSZ; };
-  auto Vt = [&](int g, int b) { return smem + SPLIT * 2 * KSZ + (g * 2 + b) * VSZ; };
-
-  // SPLIT groups of NW wavefronts take the same queries over disjoint key ranges
-  // a group is whole wavefronts (NT % 64 == 0): grp in a scalar register keeps the key tile
-  // origin, and with it the tile base address and the in-range test, scalar
-  const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), gtid = threadIdx.x % NT;
-  const int lane = threadIdx.x & 63, wave = (threadIdx.x >> 6) % NW;
-  const int c32 = lane & 31, h = lane >> 5;
-  // Workgroups go to the 8 XCDs (each with its own L2) round-robin in launch order; the
-  // first floor(n/8)*8 are renumbered so that each XCD takes a contiguous range of
-  // (sample, head, query block) triples, query blocks fastest: the query blocks of one
-  // head then read its K/V tiles through one L2 instead of all eight.
+// ---------------------------------------------------------------- bf16, two wave groups in turn
+// 8 waves of 16 QT queries in two groups of four (one wave of each group per SIMD), 64-key
+// tiles of K and V in rings of four.  Per tile a wave has a softmax slot (the tile's
+// probabilities, and the DMA of the tiles three and two ahead) and an MFMA slot (the next
+// tile's scores, then this tile's P V), each ended by a barrier; the second group runs one
+// slot behind, so that on every SIMD one wave's VALU work meets the other's MFMAs.
+// What bounds it: the card's power limit on long sequences (clock 1.86 GHz at N = 14566, H =
+// 16, d = 128; fewer VALU instructions, no bank conflicts and earlier DMA took 7 % of the
+// cycles and none of the time).  Against the kernel this replaced (32x32x16 MFMAs, both waves
+// of a SIMD in phase, K and V staged through registers): N = 14566, H = 16, d = 128 1710 ->
+// 1460 us (1190 TFLOP/s), N = 4608, H = 24 267 -> 230, N = 1536, H = 24 62 -> 40, N = 3000, H =
+// 20, d = 96 100 -> 67, B = 2, N = 1668, H = 37, d = 40 105 -> 75, B = 8, N = 256, H = 16, d =
+// 72 8.7 -> 8.0.
+// v_mfma_f32_16x16x32_bf16 layouts (A lane l: row l%16, k 8*(l/16)+0..7; B lane l: column
+// l%16, same k; D[v] at row 4*(l/16)+v, column l%16):
+//   S^T = K Q^T: lane l holds the scores of query l%16 at keys 16 i + 4 (l/16) + v, i < 4.
+//   O^T += V^T P^T, 32 keys per MFMA: k index 8 g + j stands for key 4 g + j (j < 4) of the
+//     first and 4 g + j - 4 of the second 16 keys, which makes the B operand the lane's own
+//     eight probabilities; the A operand is two transposed reads (4 keys of one dim each).
+// Head dims are zero-padded: k steps of 32 (NC), output tiles of 16 (NE); RWB bytes per LDS row.
+//
+// Ring slots: the MFMA slot of tile j reads K j+1 and V j, its first K reads going out at the
+// end of the softmax slot before.  A softmax slot i refills what the MFMA slot i-2 read
+// (K i-1, V i-2): both groups have ended that slot before either starts this one.  Before
+// the barrier that ends it, a wave waits for its DMA of the softmax slot before (K j+1 and
+// V j of the next MFMA slot's reads were issued two tiles ahead).
+template <int RWB, int NC, int NE, int QT>
+__global__ __launch_bounds__(512) void k_attn_pp(AttnArgs a) {
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the launch stub only
+  constexpr int KB = 64, NB = 4;                 // keys per tile, ring depth
+  constexpr int TB = KB * RWB;                   // bytes of a K (or V) tile
+  constexpr int DPW = RWB / 128;                 // DMA instructions per wave, tile and operand
+  constexpr int CPR = RWB / 16;                  // 16-byte chunks per LDS row
+  static_assert(NC * 64 <= RWB && NE * 32 <= RWB, "head dim tiles fit the LDS row");
+  constexpr int LDO = NE * 16 + 8;               // staged output row pitch (elements)
+  constexpr int kMain = 2 * NB * TB, kOut = 8 * 16 * QT * LDO * 2;
+  __shared__ __attribute__((aligned(1024))) char smem[kMain > kOut ? kMain : kOut];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   int qb, hd, b;
   {
-    const int nqb = (a.N + NW * 32 - 1) / (NW * 32), n = gridDim.x, id = blockIdx.x;
+    const int nqb = (a.N + 128 * QT - 1) / (128 * QT), n = gridDim.x, id = blockIdx.x;
     const int full = n / 8 * 8;
     const int t = id < full ? (id % 8) * (full / 8) + id / 8 : id;
     qb = __builtin_amdgcn_readfirstlane(t % nqb);
     hd = __builtin_amdgcn_readfirstlane((t / nqb) % a.H);
     b = __builtin_amdgcn_readfirstlane(t / (nqb * a.H));
   }
-  const int q0 = qb * (NW * 32) + wave * 32;
-  const int N = a.N, d = a.d;
-  const uint16_t* qkv = reinterpret_cast<const uint16_t*>(a.qkv);
+  const int N = a.N, d = a.d, q0 = qb * 128 * QT + wave * 16 * QT;
   const size_t rb = (size_t)b * N;
-  const size_t qoff = (size_t)hd * d, koff = (size_t)a.C + hd * d, voff = 2 * (size_t)a.C + hd * d;
-  const u32x4_t z4 = {0u, 0u, 0u, 0u};
-
-  // Q^T fragments: lane holds Q[q0 + c32][16c + 8h .. +7]
-  bf16x8_t qf[NQC];
-  {
-    const int q = q0 + c32;
+  const char* base = reinterpret_cast<const char*>(reinterpret_cast<const uint16_t*>(a.qkv) + rb * a.ldq);
+  const uint32_t ldb = (uint32_t)a.ldq * 2;
+  // Q^T fragments: lane holds Q[q0 + 16 t + l16][32 c + 8 g .. +7], zero past N and d
+  bf16x8_t qf[QT][NC];
 #pragma unroll
-    for (int c = 0; c < NQC; ++c) {
-      const int e = 16 * c + 8 * h;
-      const u32x4_t v = (q < N && e < d) ? *reinterpret_cast<const u32x4_t*>(qkv + (rb + q) * a.ldq + qoff + e) : z4;
-      qf[c] = __builtin_bit_cast(bf16x8_t, v);
+  for (int t = 0; t < QT; ++t)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int q = q0 + 16 * t + l16, e = 32 * c + 8 * g;
+      u32x4_t v = {0u, 0u, 0u, 0u};
+      if (q < N && e < d) v = *reinterpret_cast<const u32x4_t*>(base + (size_t)q * ldb + ((size_t)hd * d + e) * 2);
+      qf[t][c] = __builtin_bit_cast(bf16x8_t, v);
     }
+  // the rows of an LDS tile are rotated by f(row) among their 16-byte chunks, so that both the
+  // K reads (16 rows, one chunk) and the transposed V reads (8 rows, one chunk pair) of a
+  // pass spread over all banks
+  auto swz = [](int row) {
+    const int hi = (row >> 3) & 1;
+    return (CPR == 16 ? ((row & 7) ^ (hi << 2)) : (((row >> 1) & 3) ^ (hi << 1))) << 1 | hi;
+  };
+  uint32_t vo[DPW];   // this lane's byte offsets within a K tile; past d: out of range (zeros)
+#pragma unroll
+  for (int j = 0; j < DPW; ++j) {
+    const int idx = (wave * DPW + j) * 64 + lane, row = idx / CPR, e = ((idx % CPR) ^ swz(row)) * 8;
+    vo[j] = e < d ? (uint32_t)row * ldb + (uint32_t)e * 2 : 0x80000000u;
   }
-  f32x16_t o[NOT];
+  // DMA of the next K / V tile (c0: its column in bytes) into ring slot *slot.  The tile's own
+  // resource ends with the sample's last row, so that keys past N load as zeros.
+  auto load = [&](int off, int* tile, int* slot, uint32_t c0) __attribute__((always_inline)) {
+    const int rows = N - *tile * KB;
+    const uint64_t left = rows > 0 ? (uint64_t)rows * ldb - c0 : 0;
+    const uint32_t num = left < 0x7fffff00u ? (uint32_t)left : 0x7fffff00u;
+    __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base) + (size_t)*tile * KB * ldb + c0, 0, num, 0x00020000);
 #pragma unroll
-  for (int t = 0; t < NOT; ++t)
+    for (int j = 0; j < DPW; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, FF_AS3(smem + off + *slot + (wave * DPW + j) * 1024), 16, vo[j], 0, 0, 0);
+    ++*tile;
+    *slot = *slot == (NB - 1) * TB ? 0 : *slot + TB;
+  };
+  int ktile = 0, vtile = 0, kslot = 0, vslot = 0;
+  const uint32_t kc = ((uint32_t)a.C + (uint32_t)hd * d) * 2, vc = kc + (uint32_t)a.C * 2;
+  auto load_k = [&]() __attribute__((always_inline)) { load(0, &ktile, &kslot, kc); };
+  auto load_v = [&]() __attribute__((always_inline)) { load(NB * TB, &vtile, &vslot, vc); };
+  // fragment addresses within a tile (k step c and output tile e enter by xor)
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)smem);
+  const uint32_t ka = lds0 + l16 * RWB + ((g ^ swz(l16)) * 16);
+  const int vr = 4 * g + (l16 >> 2);
+  const uint32_t va = lds0 + NB * TB + vr * RWB + ((((l16 & 3) >> 1) ^ swz(vr)) * 16) + (l16 & 1) * 8;
+  f32x4_t o[NE][QT], sc[4][QT];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) o[t][v] = 0.f;
-  float mrow = -INFINITY, lrow = 0.f;
+  for (int e = 0; e < NE; ++e)
+#pragma unroll
+    for (int t = 0; t < QT; ++t) o[e][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m[QT], l[QT], lim[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) { m[t] = -INFINITY; l[t] = 0.f; lim[t] = -1.f; }
   const float sl2 = a.scale * 1.4426950408889634f;
-
-  // Register prefetch of one K/V tile.  K: chunk c -> key c / (DQ/8), dims (c % (DQ/8))*8.
-  // V: group g -> keys 4 (g % (KTL/4)) + 0..3, dims (g / (KTL/4))*8: each transposed row piece
-  // (4 keys of one dim) is one 8-byte LDS store, and the 16 consecutive lanes of a store
-  // fill one 128-byte V^T row segment (no bank conflicts).
-  // Each load is a uniform 64-bit tile base (the tile's first key row) plus this lane's
-  // 32-bit byte offset, fixed before the loop, so the per-tile address work is scalar and the
-  // loads take the scalar-base form.  Tiles whose chunks are all in range (every key below
-  // N, d equal to the padded head dims, every chunk owned) load without lane masks.
-  u32x4_t pk[PK], pv[PV][4];
-  uint32_t kbo[PK], vbo[PV];
-  int kkr[PK], vk4[PV];
-  bool kok[PK], vok[PV];
-  const size_t rowb = (size_t)a.ldq * 2;   // bytes per token row of qkv
+  bf16x8_t pb[2][QT];
+  int ks = 0, vs = 0;            // ring slots being read
+  // The MFMA slot of a tile is a chain of units of two A fragments and 2 QT MFMAs: first
+  // the 2 NC units of the next tile's scores (K fragments), then the NE units of this tile's
+  // PV product (V^T fragments, each two transposed reads).  A unit's reads are issued UD
+  // units ahead: LDS latency with four waves reading is longer than one unit's MFMAs.
+  constexpr int UK = 2 * NC, UV = NE, UD = 3;
+  bf16x8_t kf[UD + 1][2];
+  u32x2_t vf[UD + 1][2][2] = {};
+  uint32_t ka_ = ka, va_ = va;
+  auto rd = [&](auto Uc) __attribute__((always_inline)) {
+    constexpr int U = decltype(Uc)::value;
+    if constexpr (U < UK) {
+      constexpr int c = U / 2, i0 = U % 2 * 2;
+      const uint32_t ad = ka_ ^ (c * 64);
+      kf[U % (UD + 1)][0] = lds_rd128_at<i0 * 16 * RWB>(ad);
+      kf[U % (UD + 1)][1] = lds_rd128_at<(i0 + 1) * 16 * RWB>(ad);
+    } else if constexpr (U < UK + UV) {
+      constexpr int f = 2 * (U - UK);
+      const uint32_t a0 = va_ ^ (f % NE * 32), a1 = va_ ^ ((f + 1) % NE * 32);
+      vf[U % (UD + 1)][0][0] = lds_rd64_tr(a0, f / NE * 32 * RWB);
+      vf[U % (UD + 1)][0][1] = lds_rd64_tr(a0, f / NE * 32 * RWB + 16 * RWB);
+      vf[U % (UD + 1)][1][0] = lds_rd64_tr(a1, (f + 1) / NE * 32 * RWB);
+      vf[U % (UD + 1)][1][1] = lds_rd64_tr(a1, (f + 1) / NE * 32 * RWB + 16 * RWB);
+    }
+  };
+  auto unit = [&](auto Uc) __attribute__((always_inline)) {
+    constexpr int U = decltype(Uc)::value;
+    rd(Int<U + UD>{});
+    constexpr int later = (U + 1 < UK + UV ? (U + 1 < UK ? 2 : 4) : 0) + (U + 2 < UK + UV ? (U + 2 < UK ? 2 : 4) : 0) +
+                          (U + 3 < UK + UV ? (U + 3 < UK ? 2 : 4) : 0);
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(later) : "memory");
+    constexpr int buf = U % (UD + 1);
+    if constexpr (U < UK) {
+      FF_TIE(kf[buf][0]); FF_TIE(kf[buf][1]);
 #pragma unroll
-  for (int i = 0; i < PK; ++i) {
-    const int c = gtid + i * NT;
-    const int kr = c / (DQ / 8), e = (c % (DQ / 8)) * 8;
-    kkr[i] = kr;
-    kok[i] = c < KCH && e < d;
-    kbo[i] = kok[i] ? (uint32_t)(kr * rowb + (koff + e) * 2) : 0u;
-  }
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-  for (int i = 0; i < PV; ++i) {
-    const int g = gtid + i * NT;
-    const int k4 = (g % (KTL / 4)) * 4, e = (g / (KTL / 4)) * 8;
-    vk4[i] = k4;
-    vok[i] = g < VG && e < d;
-    vbo[i] = vok[i] ? (uint32_t)(k4 * rowb + (voff + e) * 2) : 0u;
-  }
-  const bool dense_dims = d == DQ && d == DV && KCH % NT == 0 && VG % NT == 0;
-  auto fetch = [&](int kv0) {
-    const char* tb = reinterpret_cast<const char*>(qkv + (rb + kv0) * a.ldq);
-    auto ld = [&](uint32_t off) { return *reinterpret_cast<const u32x4_t*>(tb + off); };
-    if (dense_dims && kv0 + KTL <= N) {
-#pragma unroll
-      for (int i = 0; i < PK; ++i) pk[i] = ld(kbo[i]);
-#pragma unroll
-      for (int i = 0; i < PV; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pv[i][r] = ld(vbo[i] + (uint32_t)(r * rowb));
+        for (int t = 0; t < QT; ++t) {
+          constexpr int c = U / 2, i0 = U % 2 * 2;
+          sc[i0 + i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[buf][i], qf[t][c], c == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : sc[i0 + i][t], 0, 0, 0);
+        }
     } else {
-      const int lim = N - kv0;   // keys at or past it are masked
 #pragma unroll
-      for (int i = 0; i < PK; ++i) pk[i] = (kok[i] && kkr[i] < lim) ? ld(kbo[i]) : z4;
+      for (int i = 0; i < 2; ++i) { FF_TIE(vf[buf][i][0]); FF_TIE(vf[buf][i][1]); }
 #pragma unroll
-      for (int i = 0; i < PV; ++i)
+      for (int i = 0; i < 2; ++i) {
+        constexpr int f0 = 2 * (U - UK);
+        const int s = (f0 + i) / NE, e = (f0 + i) % NE;
+        const u32x4_t w = {vf[buf][i][0][0], vf[buf][i][0][1], vf[buf][i][1][0], vf[buf][i][1][1]};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pv[i][r] = (vok[i] && vk4[i] + r < lim) ? ld(vbo[i] + (uint32_t)(r * rowb)) : z4;
+        for (int t = 0; t < QT; ++t)
+          o[e][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w), pb[s][t], o[e][t], 0, 0, 0);
+      }
     }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  auto stage = [&](int buf) {
+#define FF_BAR() asm volatile("s_barrier" ::: "memory")
+  const int nt = (N + KB - 1) / KB;
+  load_k();
+  load_k(); load_v();
+  load_k(); load_v();
+  wait_vm<2 * DPW>();
+  FF_BAR();
+  // the first tile's scores (the V reads that run ahead here are used nowhere, but hold their
+  // registers until they are in)
+  static_for<0, UD>(rd);
+  static_for<0, UK>(unit);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < PK; ++i) {
-      const int c = gtid + i * NT;
-      if (c < KCH) {
-        const int kr = c / (DQ / 8), e = (c % (DQ / 8)) * 8;
-        *reinterpret_cast<u32x4_t*>(Ks(grp, buf) + kr * LDK + e) = pk[i];
+  for (int i = 0; i < (UD + 1) * 4; ++i) FF_TIE(vf[i / 4][i / 2 % 2][i % 2]);
+  ks = TB;
+  if (wave >= 4) FF_BAR();   // the second group runs one slot behind
+  // sc -> probabilities pb (complete when it returns: nothing of it moves past the barrier)
+  auto softmax = [&]() __attribute__((always_inline)) {
+    // probabilities against the running maxima m (log2 units of the scaled scores).  m is
+    // raised, and O and l rescaled, only when a lane's 16 probabilities of a query add up to
+    // more than kPLim = 2^8 (or are not all numbers), which no tile whose scores are all at
+    // most m + 4 does: most tiles form no maximum at all.  The shift cancels in O / l, and
+    // p <= 2^8 stays well inside fp32.
+    float p[QT][16], ps[QT];
+    bool up = false;
+    auto probs = [&](int t) __attribute__((always_inline)) {
+      // m is still -inf only if every score so far is: those probabilities are 0, not NaN
+      const float mo = m[t] == -INFINITY ? 0.f : m[t];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) p[t][i] = __builtin_amdgcn_exp2f(fmaf(sc[i / 4][t][i % 4], sl2, -mo));
+      float s4[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s4[i] = (p[t][4 * i] + p[t][4 * i + 1]) + (p[t][4 * i + 2] + p[t][4 * i + 3]);
+      ps[t] = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+    };
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      probs(t);
+      up = up || !(ps[t] <= lim[t]);
+    }
+    if (__any(up)) {
+#pragma unroll
+      for (int t = 0; t < QT; ++t) {
+        float x = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x = fmaxf(x, sc[i / 4][t][i % 4]);
+        x = fmaxf(x, __shfl_xor(x, 16, 64));         // the four lanes of a query together
+        x = fmaxf(x, __shfl_xor(x, 32, 64)) * sl2;   // scale > 0: max commutes with it
+        const float mn = fmaxf(m[t], ceilf(x));      // whole: the rescale is by a power of two, exact
+        const float al = mn == m[t] ? 1.f : __builtin_amdgcn_exp2f(m[t] - mn);   // exp2(-inf) = 0
+        m[t] = mn;
+        lim[t] = mn == -INFINITY ? -1.f : kPLim;     // -1: the next tile comes here too
+        l[t] *= al;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) o[e][t] *= al;
+        probs(t);
       }
     }
 #pragma unroll
-    for (int i = 0; i < PV; ++i) {
-      const int g = gtid + i * NT;
-      if (g < VG) {
-        const int k4 = (g % (KTL / 4)) * 4, e = (g / (KTL / 4)) * 8;
-        uint16_t* dst = Vt(grp, buf) + e * LDV + vpos(k4);   // keys k4..k4+3 stay consecutive under vpos
+    for (int t = 0; t < QT; ++t) {
+      l[t] += ps[t];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          u32x2_t lo, hi;   // dims e + 2j and e + 2j + 1 of the four keys
-          lo[0] = (pv[i][0][j] & 0xffffu) | (pv[i][1][j] << 16);
-          lo[1] = (pv[i][2][j] & 0xffffu) | (pv[i][3][j] << 16);
-          hi[0] = (pv[i][0][j] >> 16) | (pv[i][1][j] & 0xffff0000u);
-          hi[1] = (pv[i][2][j] >> 16) | (pv[i][3][j] & 0xffff0000u);
-          *reinterpret_cast<u32x2_t*>(dst + (2 * j) * LDV) = lo;
-          *reinterpret_cast<u32x2_t*>(dst + (2 * j + 1) * LDV) = hi;
-        }
+      for (int s = 0; s < 2; ++s) {
+        const float* q = &p[t][8 * s];
+        const u32x4_t w = {pack_bf16x2(q[0], q[1]), pack_bf16x2(q[2], q[3]), pack_bf16x2(q[4], q[5]), pack_bf16x2(q[6], q[7])};
+        pb[s][t] = __builtin_bit_cast(bf16x8_t, w);
       }
     }
+#pragma unroll
+    for (int t = 0; t < QT; ++t) { FF_TIE(pb[0][t]); FF_TIE(pb[1][t]); FF_TIE(l[t]); }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // LDS writes done, then barrier; the global prefetch of the tile after next stays in flight
-  // (the compiler's barrier would also wait for it)
-#define FF_LDS_BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
-  // this group's tiles: [t0, t0 + nt) of the ntiles key tiles (every group runs the same
-  // number of iterations, so the workgroup barriers line up; a group past the end has
-  // kv0 >= N, all its keys masked, and contributes nothing)
-  const int ntiles = (N + KTL - 1) / KTL;
-  const int nt = (ntiles + SPLIT - 1) / SPLIT, t0 = grp * nt;
-  fetch(t0 * KTL);
-  stage(0);
-  if (nt > 1) fetch((t0 + 1) * KTL);
-  FF_LDS_BARRIER();
-  for (int kt = 0; kt < nt; ++kt) {
-    const int kv0 = (t0 + kt) * KTL, buf = kt & 1;
-    const uint16_t* K_ = Ks(grp, buf);
-    const uint16_t* V_ = Vt(grp, buf);
-    // scores for NS 32-key tiles
-    f32x16_t sc[NS];
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sc[t][v] = 0.f;
-#pragma unroll
-      for (int c = 0; c < NQC; ++c) {
-        const bf16x8_t kf = *reinterpret_cast<const bf16x8_t*>(&K_[(t * 32 + c32) * LDK + 16 * c + 8 * h]);
-        sc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[c], sc[t], 0, 0, 0);
-      }
-    }
-    // online softmax for query q0 + c32 (its KTL scores: half in this lane, half in lane ^ 32).
-    // The running max m is kept in log2 units of the scaled scores; it is raised (and O, l
-    // rescaled) only when the tile's max exceeds it by more than kLazy, so most tiles skip
-    // the rescale.  The shift cancels in O / l, and p <= 2^kLazy stays well inside fp32.
-    float mx = -INFINITY;
-    if (kv0 + KTL > N) {   // last, partial tile: keys past N get probability 0
-#pragma unroll
-      for (int t = 0; t < NS; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int key = kv0 + 32 * t + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (key >= N) sc[t][v] = -INFINITY;
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[t][v]);
-    {
-      float lo, hi;
-      wave_halves(mx, lo, hi);
-      mx = fmaxf(lo, hi) * sl2;   // scale > 0: max commutes with it
-    }
-    if (mx > mrow + kLazy) {
-      const float alpha = __builtin_amdgcn_exp2f(mrow - mx);   // v_exp_f32: exp2(-inf) = 0
-      lrow *= alpha;
-#pragma unroll
-      for (int t = 0; t < NOT; ++t) o[t] *= alpha;
-      mrow = mx;
-    }
-    // mrow is still -inf only if every score so far is -inf (all keys masked, as for a
-    // group whose keys start past N): those probabilities are exp2(-inf) = 0, not NaN
-    const float moff = mrow == -INFINITY ? 0.f : mrow;
-    float ls = 0.f;
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float pr = __builtin_amdgcn_exp2f(fmaf(sc[t][v], sl2, -moff));
-        sc[t][v] = pr;
-        ls += pr;
-      }
-    {
-      float lo, hi;
-      wave_halves(ls, lo, hi);
-      lrow += lo + hi;
-    }
-    // O^T += V^T P^T over the 16-key groups (keys 16g + ...)
-#pragma unroll
-    for (int g = 0; g < 2 * NS; ++g) {
-      const int t = g >> 1, half = g & 1;   // score tile, and which 16 keys of it
-      bf16x8_t pb;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) pb[j] = (__bf16)sc[t][8 * half + j];
-      // keys 16g + 4h + {0..3, 8..11} sit at V^T columns 16g + 8h .. +7
-#pragma unroll
-      for (int ot = 0; ot < NOT; ++ot) {
-        const bf16x8_t vf = *reinterpret_cast<const bf16x8_t*>(&V_[(ot * 32 + c32) * LDV + 16 * g + 8 * h]);
-        o[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pb, o[ot], 0, 0, 0);
-      }
-    }
-    // the other buffer held tile kt-1, which every wave finished before the last barrier
-    if (kt + 1 < nt) {
-      stage(buf ^ 1);
-      if (kt + 2 < nt) fetch(kv0 + 2 * KTL);
-    }
-    FF_LDS_BARRIER();
+  for (int kt = 0; kt < nt - 1; ++kt) {
+    load_k();
+    load_v();
+    __builtin_amdgcn_sched_barrier(0);
+    softmax();
+    ka_ = ka + ks;
+    va_ = va + vs;
+    static_for<0, UD>(rd);
+    wait_vm<2 * DPW>();
+    FF_BAR();
+    __builtin_amdgcn_s_setprio(1);
+    static_for<0, UK + UV>(unit);
+    __builtin_amdgcn_s_setprio(0);
+    FF_BAR();
+    ks = ks == (NB - 1) * TB ? 0 : ks + TB;
+    vs = vs == (NB - 1) * TB ? 0 : vs + TB;
   }
-#undef FF_LDS_BARRIER
-  if (SPLIT > 1) {
-    // merge the groups' (m, l, O) through LDS (the tile buffers are free after the last
-    // barrier): group g > 0 writes, group 0 combines in group order, exactly:
-    // m = max m_g, O = sum_g O_g 2^(m_g - m), l = sum_g l_g 2^(m_g - m)
-    constexpr int PF = NOT * 16 + 2;   // floats per lane
-    float* xch = reinterpret_cast<float*>(smem);
-    static_assert(sizeof(smem) >= (size_t)(SPLIT - 1) * NW * 64 * PF * 4, "exchange space");
-    if (grp > 0) {
-      float* p = xch + (((size_t)(grp - 1) * NW + wave) * PF) * 64 + lane;
+  // the last tile: keys past N get probability 0
 #pragma unroll
-      for (int t = 0; t < NOT; ++t)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) p[(t * 16 + v) * 64] = o[t][v];
-      p[(NOT * 16) * 64] = mrow;
-      p[(NOT * 16 + 1) * 64] = lrow;
-    }
-    __syncthreads();
-    if (grp > 0) return;
+    for (int v = 0; v < 4; ++v)
 #pragma unroll
-    for (int g2 = 1; g2 < SPLIT; ++g2) {
-      const float* p = xch + (((size_t)(g2 - 1) * NW + wave) * PF) * 64 + lane;
-      const float m2 = p[(NOT * 16) * 64], l2 = p[(NOT * 16 + 1) * 64];
-      const float mm = fmaxf(mrow, m2);
-      const float a1 = __builtin_amdgcn_exp2f(mrow - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
+      for (int t = 0; t < QT; ++t)
+        if ((nt - 1) * KB + 16 * i + 4 * g + v >= N) sc[i][t][v] = -INFINITY;
+  softmax();
+  va_ = va + vs;
+  static_for<UK, UK + UD>(rd);
+  wait_vm<0>();
+  FF_BAR();
+  static_for<UK, UK + UV>(unit);
+  FF_BAR();
+  if (wave < 4) FF_BAR();
+#undef FF_BAR
+  // o[e][t][v] = O[query q0 + 16 t + l16][16 e + 4 g + v], staged through the wave's own LDS
+  // region and stored as 16-byte row pieces; every wave's tile reads and DMA ended before
+  // the last barrier
+  uint16_t* stg = reinterpret_cast<uint16_t*>(smem) + wave * 16 * QT * LDO;
 #pragma unroll
-      for (int t = 0; t < NOT; ++t)
+  for (int t = 0; t < QT; ++t) {
+    float s = l[t] + __shfl_xor(l[t], 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    const float inv = 1.0f / s;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[t][v] = o[t][v] * a1 + p[(t * 16 + v) * 64] * a2;
-      lrow = lrow * a1 + l2 * a2;
-      mrow = mm;
-    }
+    for (int e = 0; e < NE; ++e)
+      *reinterpret_cast<u32x2_t*>(stg + (16 * t + l16) * LDO + 16 * e + 4 * g) =
+          u32x2_t{pack_bf16x2(o[e][t][0] * inv, o[e][t][1] * inv), pack_bf16x2(o[e][t][2] * inv, o[e][t][3] * inv)};
   }
-  // o[ot][v] = O[query q0 + c32][e = 32 ot + 8 (v/4) + 4 h + v%4].  In that layout a store
-  // instruction writes 8 bytes to each of 32 rows (a memory request per row), so the
-  // normalised tile goes through the wave's own LDS region as rows of bf16 and is stored
-  // as 16-byte row pieces, consecutive lanes on consecutive pieces.  The region is free:
-  // every tile read ended before the last barrier, and with SPLIT > 1 it is this wave's
-  // own merge entry, which it has finished reading (LDS ops of a wave complete in order).
-  constexpr int LDO = DV + 8;                              // staged row pitch (elements)
-  constexpr int PFX = SPLIT > 1 ? (NOT * 16 + 2) * 64 * 2 : 0;   // merge entry (elements)
-  constexpr int RW = 32 * LDO > PFX ? 32 * LDO : PFX;
-  static_assert(sizeof(smem) >= (size_t)NW * RW * 2, "output staging space");
-  uint16_t* stg = smem + wave * RW;
-  {
-    const float inv = 1.0f / lrow;
-#pragma unroll
-    for (int ot = 0; ot < NOT; ++ot)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int e = 32 * ot + 8 * g + 4 * h;
-        u32x2_t w;
-        w[0] = pack_bf16x2(o[ot][4 * g] * inv, o[ot][4 * g + 1] * inv);
-        w[1] = pack_bf16x2(o[ot][4 * g + 2] * inv, o[ot][4 * g + 3] * inv);
-        *reinterpret_cast<u32x2_t*>(stg + c32 * LDO + e) = w;
-      }
-  }
-  // d % 8 == 0 (host check): d/8 pieces per query row
   uint16_t* out = reinterpret_cast<uint16_t*>(a.out);
   const int ppr = d / 8;
-  for (int idx = lane; idx < 32 * ppr; idx += 64) {
+  for (int idx = lane; idx < 16 * QT * ppr; idx += 64) {
     const int row = idx / ppr, pc = idx - row * ppr;
-    const int qq = q0 + row;
-    if (qq < N)
-      *reinterpret_cast<u32x4_t*>(out + (rb + qq) * a.ldo + (size_t)hd * d + pc * 8) =
+    if (q0 + row < N)
+      *reinterpret_cast<u32x4_t*>(out + (rb + q0 + row) * a.ldo + (size_t)hd * d + pc * 8) =
           *reinterpret_cast<const u32x4_t*>(stg + row * LDO + pc * 8);
   }
+#endif
 }
 
 template <int D>
@@ -411,26 +373,29 @@ __global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
 hipError_t attention(int dtype, const AttnArgs& a, hipStream_t s) {
   if (a.N <= 0) return hipSuccess;
   if (dtype == DT_BF16) {
-    // a lane's byte offset within a key tile (at most 132 rows of qkv) must fit 32 bits
-    if ((uint64_t)a.ldq * 2 * 132 > 0xffffffffull) return hipErrorInvalidValue;
-    // 8 wavefronts (256 queries) per workgroup when that still gives >= 256 workgroups;
-    // else 4 wavefronts (128 queries), and when even those are fewer than 2 per CU on
-    // average, two groups of 4 over the two halves of the keys
-    const bool wide = (long)((a.N + 255) / 256) * a.H * a.B >= 256;
-    const bool split = !wide && (long)((a.N + 127) / 128) * a.H * a.B < 512 && a.N > KT;
-    const long nwg = (long)((a.N + (wide ? 255 : 127)) / (wide ? 256 : 128)) * a.H * a.B;
+    // a lane's byte offset within a 64-key tile stays below 2^31
+    if ((uint64_t)a.ldq * 2 * 64 > 0x7fffff00ull) return hipErrorInvalidValue;
+    // 16 queries per wave for d <= 64: two workgroups then share a CU (64 KB of LDS and at most
+    // 128 VGPRs each) and take 0.83 of the time of one with 32 queries (B = 2, N = 2000, H =
+    // 24, d = 64: 65 against 78 us).  For larger d 16 or 32 (QT = 2), whichever needs the
+    // shorter sum of rounds over the 256 CUs: a round with 16 takes 0.63 of one with 32 (d =
+    // 128: 1.14 against 1.80 us per 64 keys).
+    const long hb = (long)a.H * a.B, w2 = (a.N + 255) / 256 * hb, w1 = (a.N + 127) / 128 * hb;
+    const bool two = a.d > 64 && (double)((w2 + 255) / 256) <= 0.63 * ((w1 + 255) / 256);
+    const long nwg = two ? w2 : w1;
     if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nwg);   // one dimension: the kernel maps it to (sample, head, query block)
-#define FF_ATTN(DQ, DV)                                                              \
-    do {                                                                             \
-      if (wide) FF_LAUNCH((k_attn32<DQ, DV, 8, 1, 128>), grid, 512, 0, s, a);        \
-      else if (split) FF_LAUNCH((k_attn32<DQ, DV, 4, 2, 64>), grid, 512, 0, s, a);   \
-      else FF_LAUNCH((k_attn32<DQ, DV, 4, 1, 64>), grid, 256, 0, s, a);              \
+#define FF_ATTN(RWB, NC, NE)                                                          \
+    do {                                                                              \
+      if constexpr (RWB > 128)                                                        \
+        if (two) { FF_LAUNCH((k_attn_pp<RWB, NC, NE, 2>), grid, 512, 0, s, a); break; } \
+      FF_LAUNCH((k_attn_pp<RWB, NC, NE, 1>), grid, 512, 0, s, a);                     \
     } while (0)
-    if (a.d <= 64) FF_ATTN(64, 64);
-    else if (a.d <= 80) FF_ATTN(80, 96);
-    else if (a.d <= 96) FF_ATTN(96, 96);
-    else FF_ATTN(128, 128);
+    if (a.d <= 48) FF_ATTN(128, 2, 3);
+    else if (a.d <= 64) FF_ATTN(128, 2, 4);
+    else if (a.d <= 80) FF_ATTN(256, 3, 5);
+    else if (a.d <= 96) FF_ATTN(256, 3, 6);
+    else FF_ATTN(256, 4, 8);
 #undef FF_ATTN
   } else {
     dim3 grid((a.N + 63) / 64, a.H, a.B);

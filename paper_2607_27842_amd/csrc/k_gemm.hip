@@ -371,9 +371,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
 // the stage barrier orders it).  With two waves per SIMD, one wave's LDS reads and barrier
 // waits hide behind the other's MFMAs.  After the loop the second k group hands its fp32
 // sums to the first through LDS (a fixed order: group 0 + group 1), which runs the epilogue.
-#define FF_AS1(p) ((const __attribute__((address_space(1))) void*)(p))
-#define FF_AS3(p) ((__attribute__((address_space(3))) void*)(p))
-
 // Wait until at most later * PER of this wave's DMA instructions are outstanding, then
 // barrier.  A later beyond the cases waits for more than needed, which is safe.
 template <int PER>
@@ -385,13 +382,6 @@ __device__ __forceinline__ void wait_stage(int later) {
     case 2: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * PER) : "memory"); break;
     default: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * PER) : "memory"); break;
   }
-}
-
-__device__ __forceinline__ bf16x8_t lds_rd128(const uint16_t* p) {
-  u32x4_t v;
-  const uint32_t off = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)p);
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(off) : "memory");
-  return __builtin_bit_cast(bf16x8_t, v);
 }
 
 template <int BM, int BN, int WM, int WN, int NST, int EPI, bool OUT_F32, bool RES_F32, int NP>
@@ -576,23 +566,6 @@ __global__ __launch_bounds__(2 * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(Gemm
 //
 // K % 64 != 0 (K % 8 == 0): the chunks of the last stage past K are loaded from the row's
 // first chunk of that stage (in bounds) and their fragments are zeroed in registers.
-template <int OFF>
-__device__ __forceinline__ bf16x8_t lds_rd128_at(uint32_t addr) {
-  static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");
-  u32x4_t v;
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
-  return __builtin_bit_cast(bf16x8_t, v);
-}
-// the same with an offset that is a constant once the caller's loop is unrolled
-__device__ __forceinline__ bf16x8_t lds_rd128_off(uint32_t addr, int off) {
-  u32x4_t v;
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(off) : "memory");
-  return __builtin_bit_cast(bf16x8_t, v);
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-template <int V> struct Int { static constexpr int value = V; };
-
 // DMA schedule of k_gemm_pp.  A stage's operands are 4 + TN pieces (A0-A3, B0..).  Phase p of
 // stage k issues, in this order:
 //   0: A3 of stage k+1, A0 of k+2    1: B0, B1 of k+2    2: A1, B2 of k+2    3: A2, B3 of k+2
@@ -624,7 +597,6 @@ constexpr int pp_vm(int TN, int p, int left) {
     (dst)[2] = lds_rd128_at<(off) + 16 * 128>(rda[0]);               \
     (dst)[3] = lds_rd128_at<(off) + 16 * 128>(rda[1]);               \
   } while (0)
-#define FF_TIE(x) asm volatile("" : "+v"(x))
 
 template <int TN, int EPI, bool OUT_F32, bool RES_F32, int NP>
 __global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {

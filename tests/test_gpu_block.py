@@ -239,3 +239,39 @@ def test_block_gemm_tiles_off_the_64_grid(kind, H, B, lat, n_txt):
     cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
     check_block(cfg, W, seed=H)
+
+
+@pytest.mark.parametrize("d,H,B,lat", [
+    (16, 12, 2, (4, 1, 2, 4)),      # 2 keys
+    (48, 4, 1, (4, 1, 18, 14)),     # 63 keys: one tile, one short
+    (56, 4, 1, (4, 1, 16, 16)),     # 64 keys: exactly one tile
+    (64, 3, 1, (4, 1, 26, 10)),     # 65 keys: one key in the second tile
+    (80, 3, 2, (4, 1, 24, 22)),     # 132 keys, query blocks of 128 and 4
+    (88, 3, 1, (4, 1, 40, 26)),     # 260 keys
+    (104, 3, 1, (4, 1, 36, 34)),    # 306 keys, padded 128-wide tiles
+    (128, 2, 1, (4, 1, 50, 62)),    # 775 keys
+    (128, 8, 24, (4, 1, 18, 30)),   # 135 keys over 192 heads: 32 queries per wave
+    (72, 8, 24, (4, 1, 34, 30)),    # 255 keys over 192 heads: 32 queries per wave
+])
+def test_block_attention_tiles(d, H, B, lat):
+    """Attention at the edges of its 64-key tiles and query blocks, for every head-dim class."""
+    need_gpu()
+    cfg = ragged_cfg(synth.DIT, synth.BF16, d=d, H=H, B=B, lat=lat, mlp_ratio=1)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
+    check_block(cfg, W, seed=d)
+
+
+@pytest.mark.parametrize("d,H,B", [(64, 4, 1), (128, 3, 1), (128, 8, 24)])
+def test_block_attention_raised_maximum(d, H, B):
+    """Gains of 3.3 on the normalised q and k spread the scores over some +-40 (log2 units 58),
+    so that the running maximum is raised in later key tiles.  bf16 q and k (2^-9 relative
+    per element, independent) move a score of standard deviation 11 by about 0.02, and a
+    probability by 2 %; the update sums many of them."""
+    need_gpu()
+    cfg = ragged_cfg(synth.MMDIT_SINGLE, synth.BF16, d=d, H=H, n_txt=9, B=B, lat=(4, 1, 32, 36) if H < 9 else (4, 1, 18, 30),
+                     mlp_ratio=1)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.MMDIT_SINGLE)
+    W["q_g"] = W["q_g"] * np.float32(3.3)
+    W["k_g"] = synth.to_bf16_values(W["k_g"] * np.float32(3.3))
+    W["q_g"] = synth.to_bf16_values(W["q_g"])
+    check_block(cfg, W, seed=d + 1)
