@@ -6,7 +6,7 @@
 // workgroup share each 64-key tile.  Scores are formed transposed, S^T = K Q^T, so every
 // lane holds scores of ONE query (per 16-query tile), and the probabilities are already in the
 // register layout of the B operand of O^T = V^T P^T (no shuffle).
-// fp32: one thread per query, 32-key LDS tiles (small fp32 workloads only).
+// fp32: v_mfma_f32_16x16x4 in the same form, the waves of a workgroup splitting the keys.
 #include "dev_common.h"
 
 namespace ff {
@@ -311,60 +311,150 @@ __global__ __launch_bounds__(512) void k_attn_pp(AttnArgs a) {
 #endif
 }
 
-template <int D>
-__global__ __launch_bounds__(64) void k_attn_f32(AttnArgs a) {
-  constexpr int T32 = 32;
-  __shared__ float Ks[T32][D], Vs[T32][D];
-  const int lane = threadIdx.x;
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int q = blockIdx.x * 64 + lane;
-  const int N = a.N, d = a.d;
-  const float* qkv = reinterpret_cast<const float*>(a.qkv);
+// ---------------------------------------------------------------- fp32
+// v_mfma_f32_16x16x4 in the same transposed form: a workgroup's 4 waves share 16 QT queries and
+// split the keys in blocks of 32; q, K and V go from memory to registers in operand layout
+// (S^T = K Q^T takes 4 dims of a row per 16-byte chunk, one per step; in O^T = V^T P^T step
+// v takes keys 4 g + v, so the B operand is the lane's own probability), and the waves'
+// (m, l, O) are merged in wave order through LDS.  Everything stays fp32.  Bound by the fp32
+// MFMA rate and the latency of its loads; against one thread per query: N = 64, H = 4, d = 64
+// 71 -> 5 us, B = 2, N = 256, H = 16, d = 72 762 -> 16 us.
+// ND: 16-wide pieces of the head dim.
+template <int ND, int QT>
+__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+  constexpr int PF = ND * QT * 4 + 2 * QT;   // floats per lane of a merge entry
+  __shared__ float xch[3][PF][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  int qb, hd, b;
+  {
+    const int nqb = (a.N + 16 * QT - 1) / (16 * QT), n = gridDim.x, id = blockIdx.x;
+    const int full = n / 8 * 8;
+    const int t = id < full ? (id % 8) * (full / 8) + id / 8 : id;
+    qb = t % nqb; hd = (t / nqb) % a.H; b = t / (nqb * a.H);
+  }
+  const int N = a.N, d = a.d, q0 = qb * 16 * QT;
   const size_t rb = (size_t)b * N;
-  float qv[D], o[D];
+  const float* base = reinterpret_cast<const float*>(a.qkv) + rb * a.ldq + (size_t)hd * d;
+  const f32x4_t z4 = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t qf[QT][ND], o[ND][QT];
 #pragma unroll
-  for (int e = 0; e < D; ++e) {
-    qv[e] = (q < N && e < d) ? qkv[(rb + q) * a.ldq + (size_t)h * d + e] : 0.f;
-    o[e] = 0.f;
+  for (int t = 0; t < QT; ++t)
+#pragma unroll
+    for (int c = 0; c < ND; ++c) {
+      const int q = q0 + 16 * t + l16, e = 16 * c + 4 * g;
+      qf[t][c] = q < N && e < d ? *reinterpret_cast<const f32x4_t*>(base + (size_t)q * a.ldq + e) : z4;
+      o[c][t] = z4;
+    }
+  float m[QT], l[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) { m[t] = -INFINITY; l[t] = 0.f; }
+  for (int k0 = wave * 32; k0 < N; k0 += 128) {
+    f32x4_t kf[2][ND];
+    float vv[2][4][ND];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int c = 0; c < ND; ++c) {
+        const int k = k0 + 16 * i + l16, e = 16 * c + 4 * g;
+        kf[i][c] = k < N && e < d ? *reinterpret_cast<const f32x4_t*>(base + (size_t)k * a.ldq + a.C + e) : z4;
+      }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < ND; ++c) {
+          const int k = k0 + 16 * i + 4 * g + v, e = 16 * c + l16;
+          vv[i][v][c] = k < N && e < d ? base[(size_t)k * a.ldq + 2 * (size_t)a.C + e] : 0.f;
+        }
+    f32x4_t sc[2][QT];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int t = 0; t < QT; ++t) sc[i][t] = z4;
+#pragma unroll
+    for (int c = 0; c < ND; ++c)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int t = 0; t < QT; ++t) sc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[i][c][j], qf[t][c][j], sc[i][t], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      float x = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          sc[i][t][v] = k0 + 16 * i + 4 * g + v < N ? sc[i][t][v] * a.scale : -INFINITY;
+          x = fmaxf(x, sc[i][t][v]);
+        }
+      x = fmaxf(x, __shfl_xor(x, 16, 64));
+      x = fmaxf(x, __shfl_xor(x, 32, 64));
+      const float mn = fmaxf(m[t], x), mo = mn == -INFINITY ? 0.f : mn;
+      const float al = expf(m[t] - mo);   // exp(-inf) = 0
+      m[t] = mn;
+      l[t] *= al;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          sc[i][t][v] = expf(sc[i][t][v] - mo);
+          l[t] += sc[i][t][v];
+        }
+#pragma unroll
+      for (int c = 0; c < ND; ++c) o[c][t] *= al;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < ND; ++c)
+#pragma unroll
+          for (int t = 0; t < QT; ++t) o[c][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][v][c], sc[i][t][v], o[c][t], 0, 0, 0);
   }
-  float m = -INFINITY, l = 0.f;
-  for (int kv0 = 0; kv0 < N; kv0 += T32) {
-    __syncthreads();
-    for (int i = lane; i < T32 * D; i += 64) {
-      const int j = i / D, e = i % D, key = kv0 + j;
-      const bool ok = key < N && e < d;
-      Ks[j][e] = ok ? qkv[(rb + key) * a.ldq + a.C + (size_t)h * d + e] : 0.f;
-      Vs[j][e] = ok ? qkv[(rb + key) * a.ldq + 2 * (size_t)a.C + (size_t)h * d + e] : 0.f;
+  // l is per lane: the four lanes of a query add up after the merge (m is common to them)
+  if (wave > 0) {
+    float (*x)[64] = xch[wave - 1];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+#pragma unroll
+      for (int c = 0; c < ND; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[(t * ND + c) * 4 + v][lane] = o[c][t][v];
+      x[ND * QT * 4 + 2 * t][lane] = m[t];
+      x[ND * QT * 4 + 2 * t + 1][lane] = l[t];
     }
-    __syncthreads();
-    float sc[T32];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < T32; ++j) {
-      float acc = 0.f;
-#pragma unroll
-      for (int e = 0; e < D; ++e) acc = fmaf(qv[e], Ks[j][e], acc);
-      sc[j] = (kv0 + j < N) ? acc * a.scale : -INFINITY;
-      mx = fmaxf(mx, sc[j]);
-    }
-    const float mnew = fmaxf(m, mx);
-    const float alpha = expf(m - mnew);
-    l *= alpha;
-#pragma unroll
-    for (int e = 0; e < D; ++e) o[e] *= alpha;
-#pragma unroll
-    for (int j = 0; j < T32; ++j) {
-      const float p = expf(sc[j] - mnew);
-      l += p;
-#pragma unroll
-      for (int e = 0; e < D; ++e) o[e] = fmaf(p, Vs[j][e], o[e]);
-    }
-    m = mnew;
   }
-  if (q < N) {
-    float* out = reinterpret_cast<float*>(a.out);
-    const float inv = 1.0f / l;
-    for (int e = 0; e < d; ++e) out[(rb + q) * a.ldo + (size_t)h * d + e] = o[e] * inv;
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+      const float m2 = xch[w][ND * QT * 4 + 2 * t][lane], l2 = xch[w][ND * QT * 4 + 2 * t + 1][lane];
+      const float mn = fmaxf(m[t], m2), mo = mn == -INFINITY ? 0.f : mn;
+      const float a1 = expf(m[t] - mo), a2 = expf(m2 - mo);
+      m[t] = mn;
+      l[t] = l[t] * a1 + l2 * a2;
+#pragma unroll
+      for (int c = 0; c < ND; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[c][t][v] = o[c][t][v] * a1 + xch[w][(t * ND + c) * 4 + v][lane] * a2;
+    }
+    float s = l[t] + __shfl_xor(l[t], 16, 64);
+    s += __shfl_xor(s, 32, 64);
+    const float inv = 1.0f / s;
+    const int q = q0 + 16 * t + l16;
+    if (q < N) {
+      float* out = reinterpret_cast<float*>(a.out) + (rb + q) * a.ldo + (size_t)hd * d;
+#pragma unroll
+      for (int c = 0; c < ND; ++c)
+        if (16 * c + 4 * g < d) *reinterpret_cast<f32x4_t*>(out + 16 * c + 4 * g) = o[c][t] * inv;
+    }
   }
 }
 
@@ -398,9 +488,24 @@ hipError_t attention(int dtype, const AttnArgs& a, hipStream_t s) {
     else FF_ATTN(256, 4, 8);
 #undef FF_ATTN
   } else {
-    dim3 grid((a.N + 63) / 64, a.H, a.B);
-    if (a.d <= 64) FF_LAUNCH(k_attn_f32<64>, grid, 64, 0, s, a);
-    else FF_LAUNCH(k_attn_f32<128>, grid, 64, 0, s, a);
+    // 32 queries per workgroup (each K / V load feeds two query tiles) when that still gives
+    // four workgroups per CU
+    const long hb = (long)a.H * a.B;
+    const bool two = (a.N + 31) / 32 * hb >= 1024;
+    const long nwg = two ? (a.N + 31) / 32 * hb : (a.N + 15) / 16 * hb;
+    if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nwg);
+#define FF_ATTN32(ND)                                                       \
+    do {                                                                    \
+      if (two) FF_LAUNCH((k_attn_f32<ND, 2>), grid, 256, 0, s, a);          \
+      else FF_LAUNCH((k_attn_f32<ND, 1>), grid, 256, 0, s, a);              \
+    } while (0)
+    if (a.d <= 32) FF_ATTN32(2);
+    else if (a.d <= 64) FF_ATTN32(4);
+    else if (a.d <= 80) FF_ATTN32(5);
+    else if (a.d <= 96) FF_ATTN32(6);
+    else FF_ATTN32(8);
+#undef FF_ATTN32
   }
   return hipGetLastError();
 }

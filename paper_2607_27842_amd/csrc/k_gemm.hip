@@ -5,7 +5,7 @@
 // the card or K % 64 != 0, 128-row tiles of v_mfma_f32_32x32x16_bf16 (k_gemm_dl) on small
 // grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
 // rows, double buffer) covers K <= 128 off the 64 grid (the patch embedding).
-// fp32: 64x64x16 tile of plain FMAs (the small fp32 workload is launch-bound).
+// fp32: fp32 MFMAs on 16x16, 32x32 or 64x64 tiles, the waves of a tile splitting K.
 #include <algorithm>
 #include "dev_common.h"
 
@@ -17,21 +17,6 @@ namespace {
 // (a uniform branch per tile), so that a bias GEMM and a bias+GELU GEMM can share a launch.
 constexpr int EPI_BIAS_OR_GELU = 3;
 
-
-template <int EPI, bool OUT_F32, bool RES_F32, int DT>
-__device__ __forceinline__ void epilogue_store(const GemmArgs a, int r, int c, float acc) {
-  float v = acc + St<DT>::ld1(a.bias, c);
-  if (EPI == EPI_BIAS_GELU) v = gelu_tanh_f(v);
-  const size_t pr = (size_t)a.omap.phys(r);
-  if (EPI == EPI_GATED) {
-    const float res = RES_F32 ? reinterpret_cast<const float*>(a.resid)[pr * a.ldr + c]
-                              : St<DT>::ld1(a.resid, pr * a.ldr + c);
-    const float g = a.gate[(size_t)a.omap.sample(r) * a.ldg + c];
-    v = res + g * v;
-  }
-  if (OUT_F32) reinterpret_cast<float*>(a.out)[pr * a.ldo + c] = v;
-  else St<DT>::st1(a.out, pr * a.ldo + c, v);
-}
 
 // Elements (uint16) of LDS the epilogue stages per workgroup: each wave owns 32 rows of
 // its WN columns in fp32 (the worst case), rows padded by 4 floats.
@@ -787,49 +772,194 @@ __global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {
 #endif
 }
 
-// ------------------------------------------------------------------ fp32 FMA GEMM
+// ------------------------------------------------------------------ fp32 GEMM
+// v_mfma_f32_16x16x4 / 32x32x2 (fp32 in, fp32 accumulation): the card's fp32 rate with a
+// fraction of the operand traffic of plain FMAs.  The A operand holds weight rows (output
+// columns n), the B operand activation rows m, so that a lane holds 4 consecutive columns of
+// one output row.  Both operands take the same k for the same (lane group, step), in any order:
+// a lane's 16-byte chunk of 4 consecutive k feeds 4 steps.
+
+// 4 consecutive columns c.. of output row r
 template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs a) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ __attribute__((aligned(16))) float sA[TK][TM + 4];
-  __shared__ __attribute__((aligned(16))) float sB[TK][TN + 4];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int tiles_n = (a.N + TN - 1) / TN;
-  const int m0 = (blockIdx.x / tiles_n) * TM, n0 = (blockIdx.x % tiles_n) * TN;
-  const float* A = reinterpret_cast<const float*>(a.A);
-  const float* W = reinterpret_cast<const float*>(a.W);
-  const int lrow = tid >> 2, kc = (tid & 3) * 4;
-  const bool oka = m0 + lrow < a.M, okb = n0 + lrow < a.N;
-  const float* pa = A + (size_t)(oka ? a.amap.phys(m0 + lrow) : 0) * a.lda + kc;
-  const float* pb = W + (size_t)(okb ? n0 + lrow : 0) * a.ldw + kc;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < a.K; k0 += TK) {
-    const bool kin = k0 + kc < a.K;
-    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 va = (oka && kin) ? *reinterpret_cast<const float4*>(pa + k0) : z;
-    const float4 vb = (okb && kin) ? *reinterpret_cast<const float4*>(pb + k0) : z;
-    __syncthreads();
-    sA[kc + 0][lrow] = va.x; sA[kc + 1][lrow] = va.y; sA[kc + 2][lrow] = va.z; sA[kc + 3][lrow] = va.w;
-    sB[kc + 0][lrow] = vb.x; sB[kc + 1][lrow] = vb.y; sB[kc + 2][lrow] = vb.z; sB[kc + 3][lrow] = vb.w;
-    __syncthreads();
+__device__ __forceinline__ void store4_f32(const GemmArgs& a, int r, int c, f32x4_t v) {
+  const f32x4_t b = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(a.bias) + c);
+  const size_t pr = (size_t)a.omap.phys(r);
 #pragma unroll
-    for (int k = 0; k < TK; ++k) {
-      const float4 x = *reinterpret_cast<const float4*>(&sA[k][ty * 4]);
-      const float4 y = *reinterpret_cast<const float4*>(&sB[k][tx * 4]);
-      const float xa[4] = {x.x, x.y, x.z, x.w}, yb[4] = {y.x, y.y, y.z, y.w};
+  for (int e = 0; e < 4; ++e) v[e] += b[e];
+  if (EPI == EPI_BIAS_GELU) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int e = 0; e < 4; ++e) v[e] = gelu_tanh_f(v[e]);
+  }
+  if (EPI == EPI_GATED) {
+    const f32x4_t rs = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(a.resid) + pr * a.ldr + c);
+    const f32x4_t g = *reinterpret_cast<const f32x4_t*>(a.gate + (size_t)a.omap.sample(r) * a.ldg + c);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(xa[i], yb[j], acc[i][j]);
+    for (int e = 0; e < 4; ++e) v[e] = rs[e] + g[e] * v[e];
+  }
+  *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(a.out) + pr * a.ldo + c) = v;
+}
+
+// Small grids: a 16 x 16 output tile per workgroup, its 8 waves on interleaved 16-wide blocks of
+// k, operands straight from memory into registers with up to 16 loads in flight, so that K =
+// 1024 costs one memory round trip; the waves' sums are added in wave order through LDS.
+template <int EPI>
+__global__ __launch_bounds__(512) void k_gemm_f32_small(GemmArgs a) {
+  constexpr int U = 8;   // k blocks in flight per wave
+  __shared__ f32x4_t red[8][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_n = (a.N + 15) / 16;
+  const int m0 = (blockIdx.x / tiles_n) * 16, n0 = (blockIdx.x % tiles_n) * 16;
+  const int i16 = lane & 15, g = lane >> 4;
+  const int m = m0 + i16 < a.M ? m0 + i16 : m0, n = n0 + i16 < a.N ? n0 + i16 : n0;   // past the matrix: never stored
+  const float* pa = reinterpret_cast<const float*>(a.A) + (size_t)a.amap.phys(m) * a.lda + 4 * g;
+  const float* pw = reinterpret_cast<const float*>(a.W) + (size_t)n * a.ldw + 4 * g;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  const f32x4_t z = acc;
+  for (int k0 = wave * 16; k0 < a.K; k0 += 8 * 16 * U) {
+    f32x4_t x[U], w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * 128;
+      const bool in = k + 4 * g < a.K;
+      x[u] = in ? *reinterpret_cast<const f32x4_t*>(pa + k) : z;
+      w[u] = in ? *reinterpret_cast<const f32x4_t*>(pw + k) : z;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u * 128 >= a.K) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], x[u][e], acc, 0, 0, 0);
     }
   }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave) return;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 1; i < 8; ++i) {
+    const f32x4_t p = red[i][lane];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = m0 + ty * 4 + i, c = n0 + tx * 4 + j;
-      if (r < a.M && c < a.N) epilogue_store<EPI, true, true, DT_F32>(a, r, c, acc[i][j]);
+    for (int e = 0; e < 4; ++e) acc[e] += p[e];
+  }
+  if (m0 + i16 < a.M && n0 + 4 * g < a.N) store4_f32<EPI>(a, m0 + i16, n0 + 4 * g, acc);
+}
+
+// T x T output tile (32 or 64), 8 waves: T/32 x T/32 blocks of 32 x 32, KG groups of waves on
+// the k steps of a BK-wide stage; operands by DMA into a ring of four stages (rows of 128 or
+// 256 bytes, 16-byte chunks rotated by the row against bank conflicts).  Two workgroups share a
+// CU, so one's MFMAs cover the other's waits.  K % BK != 0: the last stage's chunks past K
+// load the row's first chunk of that stage (in bounds) and are zeroed after the LDS read.
+template <int T, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_f32(GemmArgs a) {
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the launch stub only
+  constexpr int NB = T / 32, KG = 8 / (NB * NB), BK = 8 * (KG < 4 ? 4 : KG), SUB = BK / 8 / KG, NST = 4;
+  constexpr int CH = BK / 4, RPI = 64 / CH, DPW = 2 * T / RPI / 8;   // chunks per row, rows and instructions per wave
+  constexpr int ROWS = 2 * T, STB = ROWS * BK * 4;
+  static_assert(DPW == 2 && SUB * KG * 8 == BK, "two DMA instructions per wave and stage");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STB];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_n = (a.N + T - 1) / T;
+  const int m0 = (blockIdx.x / tiles_n) * T, n0 = (blockIdx.x % tiles_n) * T;
+  const int blk = wave % (NB * NB), grp = wave / (NB * NB);
+  auto swz = [](int row) { return CH == 16 ? (row & 15) : ((row >> 1) & 7); };
+  const int nk = (a.K + BK - 1) / BK, kpad = nk * BK - a.K;
+  // rows 0 .. T-1 of a stage are activation rows, T .. 2T-1 weight rows
+  const char* src[DPW];
+  int back[DPW];
+#pragma unroll
+  for (int j = 0; j < DPW; ++j) {
+    const int R = (wave * DPW + j) * RPI + lane / CH, c = (lane % CH) ^ swz(R);
+    if (R < T) {
+      const int m = m0 + R < a.M ? m0 + R : m0;
+      src[j] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(a.A) + (size_t)a.amap.phys(m) * a.lda + c * 4);
+    } else {
+      const int n = n0 + R - T < a.N ? n0 + R - T : n0;
+      src[j] = reinterpret_cast<const char*>(reinterpret_cast<const float*>(a.W) + (size_t)n * a.ldw + c * 4);
     }
+    back[j] = c * 4 >= BK - kpad ? c * 16 : 0;
+  }
+  auto issue = [&](int kt) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < DPW; ++j) {
+      const char* p = src[j] + (size_t)kt * BK * 4 - (kt == nk - 1 ? back[j] : 0);
+      __builtin_amdgcn_global_load_lds(FF_AS1(p), FF_AS3(smem + (kt % NST) * STB + (wave * DPW + j) * 1024), 16, 0, 0);
+    }
+  };
+  f32x16_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  const int fr = lane & 31, fh = lane >> 5;
+  const int ra = (blk / NB) * 32 + fr, rw = T + (blk % NB) * 32 + fr;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)smem);
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nk) issue(s);
+  for (int kt = 0; kt < nk; ++kt) {
+    const int later = nk - 1 - kt;   // stages issued after this one: min(later, 2)
+    if (later >= 2) wait_vm<2 * DPW>();
+    else if (later == 1) wait_vm<DPW>();
+    else wait_vm<0>();
+    asm volatile("s_barrier" ::: "memory");   // stage kt is in; every wave is done with stage kt - 1
+    if (kt + NST - 1 < nk) issue(kt + NST - 1);
+    const uint32_t st = lds0 + (kt % NST) * STB;
+    bf16x8_t xa[SUB], xw[SUB];
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) {
+      const int c = (grp * SUB + s) * 2 + fh;
+      xa[s] = lds_rd128_off(st + ra * BK * 4 + ((c ^ swz(ra)) * 16), 0);
+      xw[s] = lds_rd128_off(st + rw * BK * 4 + ((c ^ swz(rw)) * 16), 0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) { FF_TIE(xa[s]); FF_TIE(xw[s]); }
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) {
+      f32x4_t fa = __builtin_bit_cast(f32x4_t, xa[s]), fw = __builtin_bit_cast(f32x4_t, xw[s]);
+      if (kt == nk - 1 && ((grp * SUB + s) * 2 + fh) * 4 >= BK - kpad) {
+        fa = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        fw = fa;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fw[e], fa[e], acc, 0, 0, 0);
+    }
+  }
+  __syncthreads();   // the ring is free
+  if (KG > 1) {
+    float* red = reinterpret_cast<float*>(smem) + lane;
+    if (grp > 0) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) red[(((grp - 1) * NB * NB + blk) * 16 + v) * 64] = acc[v];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int i = 0; i < KG - 1; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[v] += red[((i * NB * NB + blk) * 16 + v) * 64];
+  }
+  const int r = m0 + (blk / NB) * 32 + fr;
+  if (r >= a.M) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = n0 + (blk % NB) * 32 + 8 * q + 4 * fh;
+    if (c < a.N) store4_f32<EPI>(a, r, c, f32x4_t{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]});
+  }
+#endif
+}
+
+// The 16 x 16 tiles up to 512 of them (M = 64, N = 256, K = 1024: 6.0 us against 10.1 with 32 x 32
+// and 28 with 64 x 64 tiles; 512 x 384 x 384, 768 tiles: 6.3 against 6.0).  Against the kernel
+// these replaced (64 x 64 tiles of plain FMAs): M = 64, N = 256, K = 1024 76 -> 6 us, M = 512,
+// N = 4608, K = 1152 202 -> 75 us.
+template <int EPI>
+void launch_f32(const GemmArgs& a, hipStream_t s) {
+  const long t16 = (long)((a.M + 15) / 16) * ((a.N + 15) / 16), t32 = (long)((a.M + 31) / 32) * ((a.N + 31) / 32);
+  const long t64 = (long)((a.M + 63) / 64) * ((a.N + 63) / 64);
+  // 64 x 64 tiles take 6 + 25 us per round of 256 at K = 1152 (31 us for 72 or 216 tiles, 51 for
+  // 288 or 432, 75 for 576), 32 x 32 tiles 8 us + 0.035 us each (20 us for 288, 38 for 864)
+  const double c64 = 0.24 + (double)((t64 + 255) / 256), c32 = 0.32 + t32 / 714.0;
+  if (t16 <= 512) FF_LAUNCH(k_gemm_f32_small<EPI>, t16, 512, 0, s, a);
+  else if (c32 < c64) FF_LAUNCH((k_gemm_f32<32, EPI>), t32, 512, 0, s, a);
+  else FF_LAUNCH((k_gemm_f32<64, EPI>), t64, 512, 0, s, a);
 }
 
 template <int BM, int BN, int NP>
@@ -989,11 +1119,10 @@ hipError_t gemm_bf16(const GemmArgs* a, int n, hipStream_t s) {
 hipError_t gemm(int dtype, const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (dtype == DT_F32) {
-    const int grid = ((a.M + 63) / 64) * ((a.N + 63) / 64);
     switch (a.epi) {
-      case EPI_BIAS: FF_LAUNCH(k_gemm_f32<EPI_BIAS>, grid, 256, 0, s, a); break;
-      case EPI_BIAS_GELU: FF_LAUNCH(k_gemm_f32<EPI_BIAS_GELU>, grid, 256, 0, s, a); break;
-      default: FF_LAUNCH(k_gemm_f32<EPI_GATED>, grid, 256, 0, s, a); break;
+      case EPI_BIAS: launch_f32<EPI_BIAS>(a, s); break;
+      case EPI_BIAS_GELU: launch_f32<EPI_BIAS_GELU>(a, s); break;
+      default: launch_f32<EPI_GATED>(a, s); break;
     }
     return hipGetLastError();
   }

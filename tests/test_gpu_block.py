@@ -275,3 +275,18 @@ def test_block_attention_raised_maximum(d, H, B):
     W["k_g"] = synth.to_bf16_values(W["k_g"] * np.float32(3.3))
     W["q_g"] = synth.to_bf16_values(W["q_g"])
     check_block(cfg, W, seed=d + 1)
+
+
+@pytest.mark.parametrize("kind,H,d,B,lat,n_txt", [
+    (synth.DIT, 41, 8, 2, (4, 1, 40, 50), 0),            # 64x64 GEMM tiles, K tail of 8; two query tiles per workgroup
+    (synth.DIT, 5, 72, 1, (4, 1, 38, 26), 0),            # 32x32 tiles, K = 360 / 720 off the 64-wide stage
+    (synth.DIT, 3, 40, 1, (4, 1, 2, 2), 0),              # one token: 16x16 tiles, K = 120
+    (synth.MMDIT_DOUBLE, 2, 128, 2, (4, 1, 18, 22), 33),  # rows through a row map, 132 keys
+    (synth.MMDIT_SINGLE, 3, 96, 1, (4, 1, 16, 16), 1),   # 65 keys
+])
+def test_block_fp32_tiles(kind, H, d, B, lat, n_txt):
+    """fp32 blocks over the GEMM tile classes and attention key blocks, with tails."""
+    need_gpu()
+    cfg = ragged_cfg(kind, synth.F32, d=d, H=H, n_txt=n_txt, B=B, lat=lat)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
+    check_block(cfg, W, seed=H)
