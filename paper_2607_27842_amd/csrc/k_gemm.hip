@@ -2,8 +2,8 @@
 // through a RowMap), W [N, K] (both K-contiguous), fp32 accumulation.
 //
 // bf16: 256-row workgroup tiles of v_mfma_f32_16x16x32_bf16 (k_gemm_pp) where the grid fills
-// the card or K % 64 != 0, 128-row tiles of v_mfma_f32_32x32x16_bf16 (k_gemm_dl) on small
-// grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
+// the card, 64- and 128-row tiles of v_mfma_f32_32x32x16_bf16 whose waves split K (k_gemm_ks) on
+// small grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
 // rows, double buffer) covers K <= 128 off the 64 grid (the patch embedding).
 // fp32: fp32 MFMAs on 16x16, 32x32 or 64x64 tiles, the waves of a tile splitting K.
 #include <algorithm>
@@ -225,7 +225,7 @@ __device__ __forceinline__ int tile_of(int bid, int tm0, int tn0, int tm1, int t
 }
 
 // ------------------------------------------------------------------ bf16 MFMA GEMM
-// Register-staged fallback (K % 32 != 0): BM x BN workgroup tile, BK = 64 per LDS stage
+// Register-staged fallback (K below the other kernels' three stages): BM x BN workgroup tile, BK = 64 per LDS stage
 // with padded rows, wavefront tiles WM x WN of v_mfma_f32_32x32x16_bf16.
 constexpr int BK = 64, LDT = BK + 8;
 
@@ -329,201 +329,6 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
   // the loop ends with a barrier after every wave's last LDS read
   epilogue_block<EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, accs, smem + wave * 32 * (WN + 4) * 2);
 }
-// ------------------------------------------------------------------ bf16 MFMA GEMM, direct-to-LDS
-// For K % BKd == 0 (BKd = 32 or 64).  Operand tiles go global -> LDS with
-// global_load_lds_dwordx4 (no VGPR staging, no ds_write), into an NST-stage ring of
-// BKd-wide K slices issued NST-1 slices ahead.  Each DMA instruction fills 1 KB of LDS in
-// lane order (16 rows x 64 bytes, or 8 rows x 128 bytes), so rows cannot be padded;
-// instead lane l of a row loads a 16-byte chunk XOR-swizzled by the row ((l%4) ^
-// ((row>>2)&3), or (l%8) ^ ((row>>1)&7)), which keeps the fragment reads free of bank
-// conflicts: a 16-row group of a read spreads over all 64 banks.  (With 128-byte rows, even
-// rows sit on banks 0-31 and odd rows on 32-63, so the 64-wide swizzle takes row/2; the
-// first version used row&7, which put rows r and r+8 on the same banks.)
-//
-// Synchronisation is explicit: the compiler's barrier lowering waits for ALL outstanding
-// loads (it cannot tell which stage a DMA targets), which would remove the prefetch.  So a
-// stage boundary waits only for the next stage (s_waitcnt vmcnt(n) with the later stages
-// still in flight) and then s_barrier, as one volatile asm that is also a compiler memory
-// barrier.  Fragments are double-buffered in registers across the 16-wide k steps: the
-// reads of the next step (ds_read_b128 asm) are in flight while the MFMAs of the current
-// one run, each step waits with lgkmcnt(TM+TN) for the older reads only, and volatile "+v"
-// asms tie the fragments to the MFMAs so that none is consumed before its wait.  The one
-// barrier per stage sits between its last k step and the next stage's first.
-//
-// KG = 2 doubles the waves without growing the tile: waves w and w + NW accumulate the
-// same output block, the first over k steps 0-1 of every 64-wide stage and the second
-// over steps 2-3 (only the first issues the DMA; the second's vmcnt waits pass at once and
-// the stage barrier orders it).  With two waves per SIMD, one wave's LDS reads and barrier
-// waits hide behind the other's MFMAs.  After the loop the second k group hands its fp32
-// sums to the first through LDS (a fixed order: group 0 + group 1), which runs the epilogue.
-// Wait until at most later * PER of this wave's DMA instructions are outstanding, then
-// barrier.  A later beyond the cases waits for more than needed, which is safe.
-template <int PER>
-__device__ __forceinline__ void wait_stage(int later) {
-  static_assert(3 * PER <= 63, "vmcnt field");
-  switch (later) {
-    case 0: asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); break;
-    case 1: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(PER) : "memory"); break;
-    case 2: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * PER) : "memory"); break;
-    default: asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(3 * PER) : "memory"); break;
-  }
-}
-
-template <int BM, int BN, int WM, int WN, int NST, int EPI, bool OUT_F32, bool RES_F32, int NP>
-__global__ __launch_bounds__(2 * (BM / WM) * (BN / WN) * 64) void k_gemm_dl(GemmGroup<NP> G) {
-  constexpr int BKd = 64, KG = 2;
-  constexpr int AUX = BN == 64 ? 0 : 17;   // sc0|sc1: skips the L1 (each tile streams its panels once)
-  constexpr int NWN = BN / WN;
-  constexpr int NW = (BM / WM) * NWN;                            // output blocks (waves per k group)
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int CH = BKd / 8, RPI = 64 / CH, KS = BKd / 16;   // chunks per row, rows per DMA, k steps
-  constexpr int KPG = KS / KG;                                   // k steps per stage of one k group
-  constexpr int IA = BM / RPI / NW, IB = BN / RPI / NW;        // DMA instructions per wave per stage
-  static_assert(BKd == 32 || BKd == 64, "stage width");
-  static_assert((KG == 1 || KG == 2) && KPG % 2 == 0, "k groups take an even number of k steps");
-  static_assert(IA * RPI * NW == BM && IB * RPI * NW == BN, "every tile row loaded by one DMA lane");
-  static_assert(NST >= 3 && NST <= 5 && TM + TN <= 15, "unsupported tile");
-  constexpr int kMain = NST * (BM + BN) * BKd, kEpi = epi_lds_elems<NW, WN>();
-  constexpr int kRed = KG > 1 ? NW * TM * TN * 16 * 64 * 2 : 0;   // k group 1's partial sums (fp32)
-  __shared__ __attribute__((aligned(1024))) uint16_t smem[kMain > kEpi + kRed ? kMain : kEpi + kRed];
-  uint16_t (*sA)[BM * BKd] = reinterpret_cast<uint16_t (*)[BM * BKd]>(smem);
-  uint16_t (*sB)[BN * BKd] = reinterpret_cast<uint16_t (*)[BN * BKd]>(smem + NST * BM * BKd);
-  // wave index in a scalar register: the per-wave LDS addresses of the DMA (M0) are then
-  // computed on the scalar unit instead of with a v_readfirstlane per instruction.  With
-  // KG = 2, waves w and w + NW own the same output block (cw) and split every stage's k
-  // steps between them (k group grp); only k group 0 issues the DMA.
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = KG > 1 ? wave / NW : 0, cw = KG > 1 ? wave % NW : wave;
-  int tm, tn;
-  // workgroup-uniform: keep the problem select and tile origin in scalar registers
-  const int prob = __builtin_amdgcn_readfirstlane(tile_of(blockIdx.x, G.tm[0], G.tn[0], G.tm[NP - 1], G.tn[NP - 1], NP, tm, tn));
-  tm = __builtin_amdgcn_readfirstlane(tm);
-  tn = __builtin_amdgcn_readfirstlane(tn);
-  const GemmArgs a = (NP > 1 && prob) ? G.g[NP - 1] : G.g[0];
-  const int m0 = tm * BM, n0 = tn * BN;
-  const uint16_t* A = reinterpret_cast<const uint16_t*>(a.A);
-  const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
-  auto swz = [](int ch, int row) { return BKd == 64 ? (ch ^ ((row >> 1) & 7)) : (ch ^ ((row >> 2) & 3)); };
-  // rows past the matrix read row 0 (in bounds); their results are never stored
-  const int lr = lane / CH, ls = lane % CH;
-  size_t ga[IA], gb[IB];
-#pragma unroll
-  for (int j = 0; j < IA; ++j) {
-    const int row = (cw * IA + j) * RPI + lr, gm = m0 + row;
-    ga[j] = (size_t)a.amap.phys(gm < a.M ? gm : 0) * a.lda + swz(ls, row) * 8;
-  }
-#pragma unroll
-  for (int j = 0; j < IB; ++j) {
-    const int row = (cw * IB + j) * RPI + lr, gn = n0 + row;
-    gb[j] = (size_t)(gn < a.N ? gn : 0) * a.ldw + swz(ls, row) * 8;
-  }
-#define FF_ISSUE(st, k0)                                                                                  \
-  do {                                                                                                    \
-    if (KG == 1 || grp == 0) {                                                                            \
-      _Pragma("unroll") for (int j = 0; j < IA; ++j)                                                      \
-        __builtin_amdgcn_global_load_lds(FF_AS1(A + ga[j] + (k0)), FF_AS3(&sA[st][(cw * IA + j) * RPI * BKd]), 16, 0, AUX); \
-      _Pragma("unroll") for (int j = 0; j < IB; ++j)                                                      \
-        __builtin_amdgcn_global_load_lds(FF_AS1(W + gb[j] + (k0)), FF_AS3(&sB[st][(cw * IB + j) * RPI * BKd]), 16, 0, AUX); \
-    }                                                                                                     \
-  } while (0)
-
-  Acc32<TM, TN> accs;
-  f32x16_t (&acc)[TM][TN] = accs.t;
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int wm = (cw / NWN) * WM, wn = (cw % NWN) * WN;
-  const int fr = lane & 31, fh = lane >> 5;
-  // fragment offsets within a stage for this k group's 16-wide k steps
-  int offa[KPG][TM], offb[KPG][TN];
-#pragma unroll
-  for (int kk = 0; kk < KPG; ++kk) {
-    const int ks = grp * KPG + kk;
-#pragma unroll
-    for (int t = 0; t < TM; ++t) {
-      const int row = wm + t * 32 + fr;
-      offa[kk][t] = row * BKd + swz(ks * 2 + fh, row) * 8;
-    }
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-      const int row = wn + t * 32 + fr;
-      offb[kk][t] = row * BKd + swz(ks * 2 + fh, row) * 8;
-    }
-  }
-  const int nk = a.K / BKd;
-#pragma unroll
-  for (int s = 0; s < NST - 1; ++s)
-    if (s < nk) FF_ISSUE(s, s * BKd);
-  wait_stage<IA + IB>(min(NST - 2, nk - 1));   // stage 0 landed
-  bf16x8_t fa[2][TM], fb[2][TN];
-#pragma unroll
-  for (int t = 0; t < TM; ++t) fa[0][t] = lds_rd128(&sA[0][offa[0][t]]);
-#pragma unroll
-  for (int t = 0; t < TN; ++t) fb[0][t] = lds_rd128(&sB[0][offb[0][t]]);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int st = kt % NST;
-#pragma unroll
-    for (int s = 0; s < KPG; ++s) {
-      const int cur = s & 1, nxt = cur ^ 1;   // KPG is even: stage k step 0 is always buffer 0
-      if (s + 1 < KPG) {
-#pragma unroll
-        for (int t = 0; t < TM; ++t) fa[nxt][t] = lds_rd128(&sA[st][offa[s + 1][t]]);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) fb[nxt][t] = lds_rd128(&sB[st][offb[s + 1][t]]);
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(TM + TN) : "memory");
-      } else if (kt + 1 < nk) {
-        // stage kt+1 complete everywhere, and every wave is past its reads of stage kt-1,
-        // whose buffer now takes stage kt+NST-1; then the first k step of stage kt+1 is
-        // read while the last one of stage kt computes
-        wait_stage<IA + IB>(min(NST - 3, nk - 2 - kt));
-        if (kt + NST - 1 < nk) FF_ISSUE((kt + NST - 1) % NST, (kt + NST - 1) * BKd);
-        const int sn = (kt + 1) % NST;
-#pragma unroll
-        for (int t = 0; t < TM; ++t) fa[nxt][t] = lds_rd128(&sA[sn][offa[0][t]]);
-#pragma unroll
-        for (int t = 0; t < TN; ++t) fb[nxt][t] = lds_rd128(&sB[sn][offb[0][t]]);
-        asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(TM + TN) : "memory");
-      } else {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      }
-#pragma unroll
-      for (int t = 0; t < TM; ++t) asm volatile("" : "+v"(fa[cur][t]));
-#pragma unroll
-      for (int t = 0; t < TN; ++t) asm volatile("" : "+v"(fb[cur][t]));
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[cur][j], fa[cur][i], acc[i][j], 0, 0, 0);
-    }
-  }
-#undef FF_ISSUE
-  __syncthreads();   // every wave's last fragment reads retired before LDS is reused
-  if (KG > 1) {
-    // k group 1 hands its partial sums to k group 0 through LDS (past the epilogue staging)
-    float* red = reinterpret_cast<float*>(smem + kEpi) + cw * TM * TN * 16 * 64 + lane;
-    if (grp == 1) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) red[((i * TN + j) * 16 + v) * 64] = acc[i][j][v];
-    }
-    __syncthreads();
-    if (grp == 1) return;   // the epilogue has no workgroup barrier
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] += red[((i * TN + j) * 16 + v) * 64];
-  }
-  epilogue_block<EPI, OUT_F32, RES_F32>(a, m0 + wm, n0 + wn, accs, smem + cw * 32 * (WN + 4) * 2);
-}
-
 // ------------------------------------------------------------------ bf16 MFMA GEMM, two wave groups in turn
 // 256 x 64 TN tile (TN = 2, 3, 4), 64-wide K stages, 8 waves in two groups of four, one wave
 // of each group per SIMD.  A stage has four phases, one per 32 rows of a wave's 128 x 16 TN
@@ -772,6 +577,255 @@ __global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {
 #endif
 }
 
+// ------------------------------------------------------------------ bf16 MFMA GEMM, waves split K
+// Small grids, where 256-row tiles would leave CUs idle: BM x BN tile, 64-wide stages, 8 waves on
+// the two halves of the tile's rows and the four 16-wide k steps of a stage.
+//
+// What bounds it: LDS bandwidth.  A stage writes (BM + BN) * 128 bytes and reads (BM / 2 + BN) *
+// 256, at 128 bytes a cycle 544 cycles for 128x96, of which the MFMAs fill 386; measured 730.
+// The kernel before it split K over two groups only and read a 32-row block at a time (736 cycles
+// of LDS, 950 measured); deeper rings and prefetches into the L2 made that one slower, and
+// fragments straight from memory (16 rows x 64 bytes per load) run at a quarter of the L1's rate.
+// Alternation: waves 0-3 and 4-7, one of each per SIMD, run half a stage apart, a barrier after
+// each half, so that one's MFMAs cover the other's fragment reads and DMA.  A stage's buffer is
+// refilled from the slot after its last read on (NST - 1 stages ahead); a wave waits for its own
+// DMA of the next stage before the barrier that precedes that stage's first read.  A DMA
+// instruction fills 8 rows of 128 bytes, 16-byte chunks XOR-ed with row / 2 against bank conflicts.
+// Measured against the former kernel's best tile, us: M = 2048 N = 1152 K = 4608 37.3 -> 29.7,
+// K = 1152 15.4 -> 13.6; M = 256 K = 4608 26.7 -> 12.9; M = 1024 N = 3456 K = 1152 18.4 -> 14.1;
+// M = 1536 N = 3072 K = 15360 203 -> 174 (128x192, against 256x128 tiles of the kernel above).
+template <int BM, int BN, int NST, int EPI, bool OUT_F32, bool RES_F32, int NP>
+__global__ __launch_bounds__(512) void k_gemm_ks(GemmGroup<NP> G) {
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the launch stub only
+  constexpr int TM = BM / 64, TN = BN / 32, PN = BN <= 128 ? BN : BN / 2;   // PN: columns of an epilogue pass
+  constexpr int RB = 128, STB = (BM + BN) * RB;   // bytes of a staged row, of a stage
+  constexpr int LDR = PN + 4, kRed = 2 * BM * LDR * 4;
+  static_assert(BM % 64 == 0 && PN % 32 == 0 && NST >= 3, "tile");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STB > kRed ? NST * STB : kRed];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int tm, tn;
+  const int prob = __builtin_amdgcn_readfirstlane(tile_of(blockIdx.x, G.tm[0], G.tn[0], G.tm[NP - 1], G.tn[NP - 1], NP, tm, tn));
+  const GemmArgs a = (NP > 1 && prob) ? G.g[NP - 1] : G.g[0];
+  const int m0 = __builtin_amdgcn_readfirstlane(tm) * BM, n0 = __builtin_amdgcn_readfirstlane(tn) * BN;
+  const int half = wave & 1, kg = wave >> 1;   // this wave's rows of the tile and its k step of a stage
+  const int nk = (a.K + 63) / 64, kpad = nk * 64 - a.K;
+  const int fr = lane & 31, fh = lane >> 5;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)smem);
+  const uint32_t chunk = (uint32_t)((2 * kg + fh) ^ ((fr >> 1) & 7)) * 16;
+  uint32_t rda = lds0 + (half * (BM / 2) + fr) * RB + chunk, rdb = lds0 + (BM + fr) * RB + chunk;
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  auto loop = [&](auto Gc) __attribute__((always_inline)) {
+    constexpr int GRP = decltype(Gc)::value;              // waves 0-3 load the A rows, 4-7 the B rows
+    constexpr int ROWS = GRP ? BN : BM, PER = ROWS / 32;  // DMA instructions of a wave and stage
+    const int w4 = wave & 3;
+    const int p0 = GRP ? 0 : a.amap.phys(m0);
+    const char* base = GRP ? reinterpret_cast<const char*>(a.W) + (size_t)n0 * a.ldw * 2
+                           : reinterpret_cast<const char*>(a.A) + (size_t)p0 * a.lda * 2;
+    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, 0xffffffffu, 0x00020000);
+    uint32_t vo[PER], back[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const int R = (w4 * PER + j) * 8 + (lane >> 3);
+      const uint32_t ch = ((lane & 7) ^ ((R >> 1) & 7)) * 16;
+      // rows past the matrix read the tile's first row (in bounds); their results are never stored
+      if (GRP) vo[j] = (n0 + R < a.N ? (uint32_t)R * (uint32_t)a.ldw * 2u : 0u) + ch;
+      else vo[j] = (m0 + R < a.M ? (uint32_t)(a.amap.phys(m0 + R) - p0) * (uint32_t)a.lda * 2u : 0u) + ch;
+      // the last stage's chunks past K load the row's chunk 0 of that stage (in bounds) and are zeroed when read
+      back[j] = (kpad && ch >= (uint32_t)(64 - kpad) * 2u) ? ch : 0u;
+    }
+    char* const dst0 = smem + (GRP ? BM * RB : 0) + w4 * PER * 1024;
+    int kb = 0, ib = 0;   // the next stage to issue: byte offset along K, and its buffer
+    auto issue = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, FF_AS3(dst0 + ib + j * 1024), 16, vo[j], kb, 0, 0);
+      kb += RB;
+      ib = ib == (NST - 1) * STB ? 0 : ib + STB;
+    };
+    bf16x8_t fa[TM], fb[TN];
+    int cb = 0;
+    // the memory part of a stage; VM: DMAs of later stages that may stay outstanding
+    auto mem = [&](bool more, bool last, auto VMc) __attribute__((always_inline)) {
+#pragma unroll
+      for (int t = 0; t < TM; ++t) fa[t] = lds_rd128_off(rda, t * 32 * RB);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) fb[t] = lds_rd128_off(rdb, t * 32 * RB);
+      if (more) issue();
+      const int step = cb == (NST - 1) * STB ? -(NST - 1) * STB : STB;
+      cb += step;
+      rda += step;
+      rdb += step;
+      wait_vm<decltype(VMc)::value>();
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+      for (int t = 0; t < TM; ++t) FF_TIE(fa[t]);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) FF_TIE(fb[t]);
+      if (last && kpad) {   // both operands, so that 0 * 0 is added
+        const bool in = (2 * kg + fh) * 8 < 64 - kpad;
+        auto cut = [&](bf16x8_t& f) __attribute__((always_inline)) {
+          u32x4_t w = __builtin_bit_cast(u32x4_t, f);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = in ? w[e] : 0u;
+          f = __builtin_bit_cast(bf16x8_t, w);
+        };
+#pragma unroll
+        for (int t = 0; t < TM; ++t) cut(fa[t]);
+#pragma unroll
+        for (int t = 0; t < TN; ++t) cut(fb[t]);
+      }
+    };
+    auto mma = [&]() __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+    };
+#define FF_KS_BACK() do { _Pragma("unroll") for (int j = 0; j < PER; ++j) vo[j] -= back[j]; } while (0)
+    // nk >= NST (host check): the prologue's stages are none of them the last
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) issue();
+    wait_vm<(NST - 2) * PER>();
+    asm volatile("s_barrier" ::: "memory");
+    if (GRP) asm volatile("s_barrier" ::: "memory");   // the second group runs half a stage behind
+    for (int kt = 0; kt < nk - NST; ++kt) {
+      mem(true, false, Int<(NST - 2) * PER>{});
+      mma();
+    }
+    FF_KS_BACK();
+    mem(true, false, Int<(NST - 2) * PER>{});   // issues the last stage
+    mma();
+    static_for<0, NST - 1>([&](auto ic) __attribute__((always_inline)) {
+      constexpr int later = NST - 3 - decltype(ic)::value;
+      mem(false, decltype(ic)::value == NST - 2, Int<(later > 0 ? later : 0) * PER>{});
+      mma();
+    });
+    if (!GRP) asm volatile("s_barrier" ::: "memory");
+#undef FF_KS_BACK
+  };
+  if (wave < 4) loop(Int<0>{});
+  else loop(Int<1>{});
+  // every wave's LDS reads and DMA ended before the last barrier
+
+  // The four k steps' sums meet in LDS, PN columns at a time: 2 and 3 go to 0 and 1, then those
+  // two, from which each thread finishes pieces of 8 columns of a row.
+  constexpr int CPR = PN / 8, UNITS = BM * CPR, UPT = (UNITS + 511) / 512, TP = PN / 32;
+  constexpr bool kCache = EPI == EPI_GATED && !OUT_F32;
+  const bool want_u = kCache && a.cache_out && a.cache_u;
+  const bool gelu = EPI == EPI_BIAS_GELU || (EPI == EPI_BIAS_OR_GELU && a.epi == EPI_BIAS_GELU);
+  float* const red = reinterpret_cast<float*>(smem) + (kg & 1) * BM * LDR + (half * (BM / 2) + fr) * LDR + 4 * fh;
+  static_for<0, BN / PN>([&](auto passc) __attribute__((always_inline)) {
+    constexpr int J0 = decltype(passc)::value * TP;
+    u32x4_t bias[UPT], resb[UPT], uu[UPT];
+    f32x4_t resf[UPT][2], gate[UPT][2];
+    size_t po[UPT];
+    bool ok[UPT];
+    auto request = [&]() __attribute__((always_inline)) {   // what the pass needs from memory
+#pragma unroll
+      for (int q = 0; q < UPT; ++q) {
+        const int p = q * 512 + threadIdx.x, r = m0 + p / CPR, c = n0 + J0 * 32 + p % CPR * 8;
+        ok[q] = p < UNITS && r < a.M && c < a.N;   // N % 8 == 0: a piece is in range as a whole
+        const int rr = ok[q] ? r : m0, cc = ok[q] ? c : n0;
+        const size_t pr = (size_t)a.omap.phys(rr);
+        po[q] = pr * a.ldo + cc;
+        bias[q] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.bias) + cc);
+        if (EPI == EPI_GATED) {
+          if (RES_F32) {
+            const float* rp = reinterpret_cast<const float*>(a.resid) + pr * a.ldr + cc;
+            resf[q][0] = *reinterpret_cast<const f32x4_t*>(rp);
+            resf[q][1] = *reinterpret_cast<const f32x4_t*>(rp + 4);
+          } else {
+            resb[q] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.resid) + pr * a.ldr + cc);
+          }
+          const float* gp = a.gate + (size_t)a.omap.sample(rr) * a.ldg + cc;
+          gate[q][0] = *reinterpret_cast<const f32x4_t*>(gp);
+          gate[q][1] = *reinterpret_cast<const f32x4_t*>(gp + 4);
+        }
+        if (want_u) uu[q] = *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const uint16_t*>(a.cache_u) + po[q]);
+      }
+    };
+    auto put = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TP; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<f32x4_t*>(red + i * 32 * LDR + j * 32 + 8 * v) =
+                f32x4_t{acc[i][J0 + j][4 * v], acc[i][J0 + j][4 * v + 1], acc[i][J0 + j][4 * v + 2], acc[i][J0 + j][4 * v + 3]};
+    };
+    // the loads come before the exchange where the registers allow
+    if (BN == PN) request();
+    if (J0) __syncthreads();   // the last pass's reads
+    if (kg >= 2) put();
+    __syncthreads();
+    if (kg < 2) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TP; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const f32x4_t p = *reinterpret_cast<const f32x4_t*>(red + i * 32 * LDR + j * 32 + 8 * v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[i][J0 + j][4 * v + e] += p[e];
+          }
+      put();   // where this lane alone has read
+    }
+    if (BN != PN) request();
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < UPT; ++q) {
+      if (!ok[q]) continue;
+      const int p = q * 512 + threadIdx.x;
+      const float* l = reinterpret_cast<const float*>(smem) + (p / CPR) * LDR + p % CPR * 8;
+      float v[8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const f32x4_t x = *reinterpret_cast<const f32x4_t*>(l + 4 * h), y = *reinterpret_cast<const f32x4_t*>(l + BM * LDR + 4 * h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[4 * h + e] = x[e] + y[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] += __uint_as_float(e & 1 ? bias[q][e / 2] & 0xffff0000u : bias[q][e / 2] << 16);
+        if (gelu) v[e] = gelu_tanh_f(v[e]);
+        if (EPI == EPI_GATED) {
+          const float rs = RES_F32 ? resf[q][e / 4][e % 4] : __uint_as_float(e & 1 ? resb[q][e / 2] & 0xffff0000u : resb[q][e / 2] << 16);
+          v[e] = rs + gate[q][e / 4][e % 4] * v[e];
+        }
+      }
+      if (OUT_F32) {
+        St<DT_F32>::store(a.out, po[q], v);
+        St<DT_F32>::store(a.out, po[q] + 4, v + 4);
+        continue;
+      }
+      St<DT_BF16>::store(a.out, po[q], v);
+      if (kCache && a.cache_out) {   // history refresh from the stored (rounded) output
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[e] = St<DT_BF16>::rnd(v[e]);
+          if (want_u) v[e] -= __uint_as_float(e & 1 ? uu[q][e / 2] & 0xffff0000u : uu[q][e / 2] << 16);
+        }
+        St<DT_BF16>::store(a.cache_out, po[q], v);
+      }
+    }
+  });
+#endif
+}
+
 // ------------------------------------------------------------------ fp32 GEMM
 // v_mfma_f32_16x16x4 / 32x32x2 (fp32 in, fp32 accumulation): the card's fp32 rate with a
 // fraction of the operand traffic of plain FMAs.  The A operand holds weight rows (output
@@ -987,18 +1041,6 @@ void launch_tile(const GemmArgs* a, int n, hipStream_t s) {
   }
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int EPI, bool OF, bool RF>
-void launch_dl(const GemmArgs* a, int n, hipStream_t s) {
-  int nwg;
-  if (n == 1) {
-    const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, EPI, OF, RF, 1>), nwg, 2 * (BM / WM) * (BN / WN) * 64, 0, s, G);
-  } else {
-    const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_dl<BM, BN, WM, WN, NST, EPI, OF, RF, 2>), nwg, 2 * (BM / WM) * (BN / WN) * 64, 0, s, G);
-  }
-}
-
 template <int TN, int EPI, bool OF, bool RF>
 void launch_pp(const GemmArgs* a, int n, hipStream_t s) {
   int nwg;
@@ -1011,25 +1053,43 @@ void launch_pp(const GemmArgs* a, int n, hipStream_t s) {
   }
 }
 
-// Tile choice: the candidate with the least estimated time.  A candidate's round of
-// workgroups over the 256 CUs takes lat + k * K us when it is bound by its own chain of
-// stages, and its tiles keep the whole card busy for pow us per 256 tiles and unit of K when
-// the card's power limit binds (large grids: the clock falls to about 1.6 GHz, so that a
-// grid that leaves CUs idle runs its tiles faster).  Measured on MI355X with random bf16
-// data; 256 x 64 TN tiles run k_gemm_pp, 128-row tiles k_gemm_dl.  In us at K = 1152 / 4608 /
-// 15360 for one round of few tiles: 256x256 31 / 85 / 230, 256x192 28 / 70 / 188, 256x128
-// 21 / 57 / 159, 128x96 15 / 37 / -, 128x64 10 / 29 / -; a full round at K = 3072 (clock
-// down): 77, 62, 47 us.  What the choice picks, against the kernels this replaced (256x256 and
-// 256x192 of 32x32x16 MFMAs with one wait and barrier per stage, 128x128 two per CU): M = 4608,
-// N = 21504, K = 3072 545 -> 460 us (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us,
-// 14310 x 8192 x 2048 440 -> 370 us, 8192 x 4608 x 1152 100 -> 89 us, 2048 x 3456 x 1152
-// 26.1 -> 20.8 us.
-enum { kTile256, kTile256x192, kTile256x128, kTile128, kTile128x96, kTile128x64, kTileCount };
+template <int BM, int BN, int NST, int EPI, bool OF, bool RF>
+void launch_ks(const GemmArgs* a, int n, hipStream_t s) {
+  int nwg;
+  if (n == 1) {
+    const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
+    FF_LAUNCH((k_gemm_ks<BM, BN, NST, EPI, OF, RF, 1>), nwg, 512, 0, s, G);
+  } else {
+    const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
+    FF_LAUNCH((k_gemm_ks<BM, BN, NST, EPI, OF, RF, 2>), nwg, 512, 0, s, G);
+  }
+}
+
+// Tile choice: the candidate with the least estimated time.  A round of workgroups takes
+// lat + k * K us, bound by its own chain of stages, and 256-row tiles keep the whole card busy for
+// pow us per 256 tiles and unit of K when the card's power limit binds (large grids: the clock
+// falls to about 1.6 GHz, so that a grid that leaves CUs idle runs its tiles faster); the smaller
+// tiles' pow is their share of the L2 at long K (1536 x 3072 x 15360: 128x96 223 us, 128x192 174).  Tiles that
+// leave room for a second workgroup per CU take lat2 + k2 * K for a round of 257 to 512.
+// Measured on MI355X with random bf16 data; 256-row tiles run k_gemm_pp, the others k_gemm_ks.
+// In us at K = 1152 / 4608 for one round of few tiles: 256x256 31 / 85, 256x192 28 / 70, 256x128
+// 21 / 57-69, 128x192 19 / 58, 128x128 15 / 33, 128x96 13.6 / 30, 128x64 9.3 / 22.5, 64x96 8.1 / 19,
+// 64x64 7.0 / 15.6 (288 tiles: 10.3 / 26.7), 64x32 6.1 / 12.9 (288: 8.2 / 20.5), 64x96 with 384 tiles 14.5 / 37; a full round at K =
+// 3072 (clock down): 77, 62, 47 us for the 256-row tiles.
+// What the 256-row tiles take against the kernels before them (256x256 and 256x192 of 32x32x16
+// MFMAs with one wait and barrier per stage): M = 4608, N = 21504, K = 3072 545 -> 460 us
+// (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us, 14310 x 8192 x 2048 440 -> 370 us.
+enum { kTile256, kTile256x192, kTile256x128, kTile128x192, kTile128, kTile128x96, kTile128x64, kTile64x96, kTile64,
+       kTile64x32, kTileCount };
+constexpr int ks_nst(int tile) { return tile == kTile128 || tile == kTile64 ? 5 : tile == kTile64x32 ? 6 : 4; }
 struct TilePlan { int tile; double cost; };
-struct TileCost { int bm, bn; double lat, k, pow; };
+struct TileCost { int bm, bn; double lat, k, pow, lat2, k2; };
 constexpr TileCost kTileCost[kTileCount] = {
-    {256, 256, 15.0, 0.0150, 0.0245}, {256, 192, 13.0, 0.0122, 0.0192}, {256, 128, 9.0, 0.0103, 0.0145},
-    {128, 128, 9.5, 0.0076, 0.0145},  {128, 96, 8.3, 0.0062, 0.0120},   {128, 64, 4.2, 0.0054, 0.0100}};
+    {256, 256, 15.0, 0.0150, 0.0245, 0, 0},  {256, 192, 13.0, 0.0122, 0.0192, 0, 0},
+    {256, 128, 7.5, 0.0118, 0.0145, 0, 0},   {128, 192, 8.0, 0.0108, 0, 0, 0},
+    {128, 128, 8.0, 0.0058, 0.0140, 0, 0},   {128, 96, 8.0, 0.0048, 0.0095, 0, 0},
+    {128, 64, 4.8, 0.0039, 0.0095, 0, 0},         {64, 96, 4.6, 0.0032, 0.0045, 6.5, 0.0062},
+    {64, 64, 4.2, 0.0025, 0.0048, 5.0, 0.0047}, {64, 32, 3.9, 0.0020, 0.0028, 4.0, 0.0036}};
 
 long tiles_of(const GemmArgs* a, int n, int bm, int bn) {
   long t = 0;
@@ -1037,34 +1097,32 @@ long tiles_of(const GemmArgs* a, int n, int bm, int bn) {
   return t;
 }
 
-bool all_k(const GemmArgs* a, int n, int m) {
-  for (int i = 0; i < n; ++i)
-    if (a[i].K % m) return false;
-  return true;
-}
-
-// k_gemm_pp takes three or more 64-wide stages, and its operand rows lie within a 32-bit byte
-// offset of their tile's first row (256 consecutive rows of a row map span at most
-// 255 / n_seg + 1 further samples).
-bool pp_ok(const GemmArgs* a, int n) {
+// Operand rows lie within a 32-bit byte offset of their tile's first row (256 consecutive rows
+// of a row map span at most 255 / n_seg + 1 further samples, and no more than there are).
+bool dma_ok(const GemmArgs* a, int n) {
   for (int i = 0; i < n; ++i) {
     const RowMap& m = a[i].amap;
-    const uint64_t span = m.n_seg == m.N ? 256 : (uint64_t)(255 / m.n_seg + 1) * m.N + 256;
-    if (a[i].K <= 128 || span * a[i].lda * 2 > 0xf0000000ull || 256ull * a[i].ldw * 2 > 0xf0000000ull) return false;
+    const int more = std::min(255 / m.n_seg + 1, (a[i].M - 1) / m.n_seg);
+    const uint64_t span = m.n_seg == m.N ? 256 : (uint64_t)more * m.N + 256;
+    if (span * a[i].lda * 2 > 0xf0000000ull || 256ull * a[i].ldw * 2 > 0xf0000000ull) return false;
   }
   return true;
 }
 
 TilePlan plan_tiles(const GemmArgs* a, int n) {
-  const bool pp = pp_ok(a, n), ring = all_k(a, n, 64);
-  int K = 0;
-  for (int i = 0; i < n; ++i) K = std::max(K, a[i].K);
   TilePlan best{-1, 1e300};
+  if (!dma_ok(a, n)) return best;
+  int K = 0, nk = 1 << 30;
+  for (int i = 0; i < n; ++i) {
+    K = std::max(K, a[i].K);
+    nk = std::min(nk, (a[i].K + 63) / 64);
+  }
   for (int c = 0; c < kTileCount; ++c) {
-    if (c < kTile128 ? !pp : !ring) continue;
+    if (nk < (c <= kTile256x128 ? 3 : ks_nst(c))) continue;   // the stages that the kernel's prologue takes
     const TileCost& t = kTileCost[c];
-    const long tiles = tiles_of(a, n, t.bm, t.bn);
-    const double cost = std::max((double)((tiles + 255) / 256) * (t.lat + t.k * K), tiles / 256.0 * t.pow * K);
+    const long tiles = tiles_of(a, n, t.bm, t.bn), slots = t.lat2 > 0 ? 512 : 256, rest = tiles % slots;
+    const double one = t.lat + t.k * K, full = t.lat2 > 0 ? t.lat2 + t.k2 * K : one;
+    const double cost = std::max(tiles / slots * full + (rest == 0 ? 0 : rest <= 256 ? one : full), tiles / 256.0 * t.pow * K);
     if (cost < best.cost) best = TilePlan{c, cost};
   }
   return best;
@@ -1076,9 +1134,13 @@ void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
     case kTile256: launch_pp<4, EPI, OF, RF>(a, n, s); break;
     case kTile256x192: launch_pp<3, EPI, OF, RF>(a, n, s); break;
     case kTile256x128: launch_pp<2, EPI, OF, RF>(a, n, s); break;
-    case kTile128: launch_dl<128, 128, 64, 64, 4, EPI, OF, RF>(a, n, s); break;
-    case kTile128x96: launch_dl<128, 96, 32, 96, 4, EPI, OF, RF>(a, n, s); break;
-    case kTile128x64: launch_dl<128, 64, 32, 64, 4, EPI, OF, RF>(a, n, s); break;
+    case kTile128x192: launch_ks<128, 192, ks_nst(kTile128x192), EPI, OF, RF>(a, n, s); break;
+    case kTile128: launch_ks<128, 128, ks_nst(kTile128), EPI, OF, RF>(a, n, s); break;
+    case kTile128x96: launch_ks<128, 96, ks_nst(kTile128x96), EPI, OF, RF>(a, n, s); break;
+    case kTile128x64: launch_ks<128, 64, ks_nst(kTile128x64), EPI, OF, RF>(a, n, s); break;
+    case kTile64x96: launch_ks<64, 96, ks_nst(kTile64x96), EPI, OF, RF>(a, n, s); break;
+    case kTile64: launch_ks<64, 64, ks_nst(kTile64), EPI, OF, RF>(a, n, s); break;
+    case kTile64x32: launch_ks<64, 32, ks_nst(kTile64x32), EPI, OF, RF>(a, n, s); break;
     default: launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s); break;   // K <= 128 off the 64 grid
   }
 }

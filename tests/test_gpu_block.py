@@ -241,6 +241,24 @@ def test_block_gemm_tiles_off_the_64_grid(kind, H, B, lat, n_txt):
     check_block(cfg, W, seed=H)
 
 
+@pytest.mark.parametrize("kind,H,B,lat,n_txt", [
+    (synth.DIT, 33, 1, (4, 1, 22, 60), 0),              # M = 330, K = 264 (five stages: the least for 64x64) / 528: 64x64, 64x32
+    (synth.DIT, 49, 3, (4, 1, 40, 50), 0),              # M = 1500, K = 392 / 784: 128x64, 64x64, 64x96
+    (synth.DIT, 65, 3, (4, 1, 56, 50), 0),              # M = 2100, K = 520 / 1040: 128x128, two 64x96 per CU
+    (synth.DIT, 89, 2, (4, 1, 52, 100), 0),             # M = 2600, K = 712 / 1424: 128x192 (two epilogue passes), 128x128, 128x64
+    (synth.DIT, 144, 8, (4, 1, 32, 30), 0),             # M = 1920, K = 1152 / 2304: 128x96
+    (synth.MMDIT_DOUBLE, 49, 4, (4, 1, 18, 22), 13),    # text and image rows of four samples through a row map
+    (synth.MMDIT_SINGLE, 41, 1, (4, 1, 20, 30), 7),     # K = 328 / 984, bias and bias + GELU in one launch
+])
+def test_block_gemm_tiles_split_k(kind, H, B, lat, n_txt):
+    """The GEMM tiles whose waves split K, small grids: row, column and K tails, the fewest
+    stages of a tile, grouped problems."""
+    need_gpu()
+    cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
+    check_block(cfg, W, seed=H)
+
+
 @pytest.mark.parametrize("d,H,B,lat", [
     (16, 12, 2, (4, 1, 2, 4)),      # 2 keys
     (48, 4, 1, (4, 1, 18, 14)),     # 63 keys: one tile, one short
