@@ -1,6 +1,7 @@
 // Normalisation (adaLN-modulated LayerNorm, per-head QK RMSNorm), the modulation /
 // time-embedding GEMV, and the once-per-step latent kernels (patchify, sinusoidal
 // time embedding, unpatchify fused with the Euler update).
+#include <algorithm>
 #include "dev_common.h"
 
 namespace ff {
@@ -165,89 +166,89 @@ __global__ __launch_bounds__(256) void k_ln_modulate(LnModArgs a) {
   }
 }
 
-// One thread per (row, head): in-place RMSNorm over the head's d elements.
+// q and k heads of a row: each lane owns one 16-byte chunk of a head (lph = d / V lanes a head,
+// hw = 64 / lph heads a wavefront at a time), the lanes of a head add their sums of squares with
+// shuffles (fixed order), and every lane rescales its own chunk.  A wavefront takes every
+// parts-th group of hw heads of its row, four groups' loads at a time.  A lane's chunk has the
+// same place in each of its heads, so the rotation's angles, sines and cosines are formed once
+// per row and lane: the kernel is bound by memory where it was bound by sincosf when it formed
+// them per head.
 template <int DT>
-__global__ __launch_bounds__(256) void k_rms_heads(RmsArgs a) {
+__global__ __launch_bounds__(256) void k_rms_qk(RmsQKArgs a, int parts) {
   using S = St<DT>;
-  const long t = (long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (long)a.rows * a.H) return;
-  const int r = (int)(t / a.H), h = (int)(t % a.H);
-  const size_t base = (size_t)a.map.phys(r) * a.ld + a.col0 + (size_t)h * a.d;
-  float ss = 0.f;
-  for (int e = 0; e < a.d; e += 4) {
-    float v[4];
-    ld4<DT>(a.x, base + e, v);
-    ss += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-  }
-  const float inv = 1.0f / sqrtf(ss / (float)a.d + a.eps);
-  for (int e = 0; e < a.d; e += 4) {
-    float v[4];
-    ld4<DT>(a.x, base + e, v);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = v[j] * inv * S::ld1(a.g, e + j);
-    st4<DT>(a.x, base + e, v);
-  }
-}
-
-// q and k of a row in one pass: each lane owns one 16-byte chunk of the row's [q | k]
-// columns, the LPH = d / V lanes of a head add their sums of squares with xor shuffles
-// (fixed order), and every lane rescales its own chunk.  One wavefront covers 64 chunks.
-template <int DT, int LPH>
-__global__ __launch_bounds__(256) void k_rms_qk(RmsQKArgs a) {
-  using S = St<DT>;
+  constexpr int V = S::V, UN = 4;
   const int lane = threadIdx.x & 63;
   const long wv = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int span = 2 * a.H * a.d;                 // q and k columns
-  const int nseg = (span + 64 * S::V - 1) / (64 * S::V);
-  const long r = wv / nseg;
+  const long r = wv / parts;
   if (r >= a.rows) return;                        // whole wavefront, no barrier below
-  const int col = (int)(wv % nseg) * 64 * S::V + lane * S::V;
-  const bool on = col < span;
-  const size_t base = (size_t)a.map.phys((int)r) * a.ld;
-  const int qk = col >= a.H * a.d;
-  const int e = (col - qk * a.H * a.d) % a.d;   // a multiple of V: the gain chunk is one access
-  const void* g = qk ? a.gk : a.gq;
-  float v[S::V], gv[S::V];
-  float ss = 0.f;
-  if (on) {
-    // the gain chunk is requested with the row chunk (read after the reduction, one
-    // element at a time, each of its loads waited on its own)
-    S::load(a.x, base + col, v);
-    S::load(g, e, gv);
+  const int part = (int)(wv % parts);
+  const int lph = a.d / V, hw = 64 / lph, sub = lane / lph, e = lane % lph * V, groups = (2 * a.H + hw - 1) / hw;
+  const bool pow2 = (lph & (lph - 1)) == 0;
+  const size_t base = (size_t)a.map.phys((int)r) * a.ld + e;
+  float gq[V], gk[V], sn[V / 2], cs[V / 2];
+  if ((((uintptr_t)a.gq | (uintptr_t)a.gk) & 15) == 0) {
+    S::load(a.gq, e, gq);
+    S::load(a.gk, e, gk);
+  } else {
 #pragma unroll
-    for (int j = 0; j < S::V; ++j) ss = fmaf(v[j], v[j], ss);
+    for (int j = 0; j < V; ++j) { gq[j] = S::ld1(a.gq, e + j); gk[j] = S::ld1(a.gk, e + j); }
   }
-#pragma unroll
-  for (int o = LPH / 2; o >= 1; o /= 2) ss += __shfl_xor(ss, o, 64);
-  if (!on) return;
-  const float inv = 1.0f / sqrtf(ss / (float)a.d + a.eps);
-#pragma unroll
-  for (int j = 0; j < S::V; ++j) v[j] = v[j] * inv * gv[j];
   const Rope& ro = a.rope;
-  if (ro.axes[0] + ro.axes[1] + ro.axes[2]) {
-    // the row's token n within its sample; image rows carry (frame, row, column) ids
-    const int n = a.map.off + (int)(r % a.map.n_seg);
-    if (n >= ro.n_txt) {
-      const int t = n - ro.n_txt;
-      const float pos[3] = {(float)(t / (ro.Hp * ro.Wp)), (float)((t / ro.Wp) % ro.Hp), (float)(t % ro.Wp)};
+  // the row's token n within its sample; image rows carry (frame, row, column) ids
+  const int n = a.map.off + (int)(r % a.map.n_seg);
+  const bool turn = ro.axes[0] + ro.axes[1] + ro.axes[2] && n >= ro.n_txt;
+  if (turn) {
+    const int t = n - ro.n_txt;
+    const float pos[3] = {(float)(t / (ro.Hp * ro.Wp)), (float)((t / ro.Wp) % ro.Hp), (float)(t % ro.Wp)};
 #pragma unroll
-      for (int j = 0; j < S::V; j += 2) {   // e + j is even: a lane holds whole pairs
-        int p = e + j, ax = 0;
-        if (p >= ro.axes[0]) { p -= ro.axes[0]; ax = 1; if (p >= ro.axes[1]) { p -= ro.axes[1]; ax = 2; } }
-        // selects, not ro.axes[ax] / pos[ax]: a lane-varying index into the argument block
-        // became a memory load (and a wait) per pair
-        const int da = ax == 0 ? ro.axes[0] : (ax == 1 ? ro.axes[1] : ro.axes[2]);
-        const float ps = ax == 0 ? pos[0] : (ax == 1 ? pos[1] : pos[2]);
-        const float w = exp2f(-(float)p / (float)da * ro.log2_theta);   // theta^(-2i/da), p = 2i
-        float sn, cs;
-        sincosf(ps * w, &sn, &cs);
-        const float x0 = v[j], x1 = v[j + 1];
-        v[j] = x0 * cs - x1 * sn;
-        v[j + 1] = x0 * sn + x1 * cs;
-      }
+    for (int j = 0; j < V; j += 2) {   // e + j is even: a lane holds whole pairs
+      int p = e + j, ax = 0;
+      if (p >= ro.axes[0]) { p -= ro.axes[0]; ax = 1; if (p >= ro.axes[1]) { p -= ro.axes[1]; ax = 2; } }
+      // selects, not ro.axes[ax] / pos[ax]: a lane-varying index into the argument block
+      // became a memory load (and a wait) per pair
+      const int da = ax == 0 ? ro.axes[0] : (ax == 1 ? ro.axes[1] : ro.axes[2]);
+      const float ps = ax == 0 ? pos[0] : (ax == 1 ? pos[1] : pos[2]);
+      const float w = exp2f(-(float)p / (float)da * ro.log2_theta);   // theta^(-2i/da), p = 2i
+      sincosf(ps * w, &sn[j / 2], &cs[j / 2]);
     }
   }
-  S::store(a.x, base + col, v);
+  for (int g0 = part; g0 < groups; g0 += UN * parts) {
+    float v[UN][V];
+    bool on[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int h = (g0 + u * parts) * hw + sub;
+      on[u] = sub < hw && h < 2 * a.H;
+      S::load(a.x, base + (size_t)(on[u] ? h : 0) * a.d, v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int h = (g0 + u * parts) * hw + sub;
+      float ss = 0.f;
+#pragma unroll
+      for (int j = 0; j < V; ++j) ss = fmaf(v[u][j], v[u][j], ss);
+      if (pow2) {
+        for (int o = lph / 2; o >= 1; o /= 2) ss += __shfl_xor(ss, o, 64);
+      } else {
+        float sum = 0.f;
+        for (int i = 0; i < lph; ++i) sum += __shfl(ss, (sub * lph + i) & 63, 64);
+        ss = sum;
+      }
+      if (!on[u]) continue;
+      const float inv = 1.0f / sqrtf(ss / (float)a.d + a.eps);
+#pragma unroll
+      for (int j = 0; j < V; ++j) v[u][j] = v[u][j] * inv * (h < a.H ? gq[j] : gk[j]);
+      if (turn) {
+#pragma unroll
+        for (int j = 0; j < V; j += 2) {
+          const float x0 = v[u][j], x1 = v[u][j + 1];
+          v[u][j] = x0 * cs[j / 2] - x1 * sn[j / 2];
+          v[u][j + 1] = x0 * sn[j / 2] + x1 * cs[j / 2];
+        }
+      }
+      S::store(a.x, base + (size_t)h * a.d, v[u]);
+    }
+  }
 }
 
 constexpr int kGemvTileB = 8;   // samples per launch of the generic tile
@@ -897,37 +898,16 @@ hipError_t ln_modulate(int dtype, const LnModArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t rms_heads(int dtype, const RmsArgs& a, hipStream_t s) {
-  if (a.rows == 0) return hipSuccess;
-  const int grid = cdiv((long)a.rows * a.H, 256);
-  if (dtype == DT_BF16) FF_LAUNCH(k_rms_heads<DT_BF16>, grid, 256, 0, s, a);
-  else FF_LAUNCH(k_rms_heads<DT_F32>, grid, 256, 0, s, a);
-  return hipGetLastError();
-}
-
 hipError_t rms_qk(int dtype, const RmsQKArgs& a, hipStream_t s) {
   if (a.rows == 0) return hipSuccess;
-  const int V = dtype == DT_BF16 ? 8 : 4;
-  const int lph = a.d / V;
-  const bool fast = a.d % V == 0 && (lph == 8 || lph == 16 || lph == 32) && (64 * V) % a.d == 0;
-  if (!fast) {   // per-head thread kernel, q then k
-    RmsArgs q{a.x, a.ld, a.map, a.rows, a.H, a.d, 0, a.gq, a.eps};
-    hipError_t e = rms_heads(dtype, q, s);
-    if (e != hipSuccess) return e;
-    RmsArgs k{a.x, a.ld, a.map, a.rows, a.H, a.d, a.H * a.d, a.gk, a.eps};
-    return rms_heads(dtype, k, s);
-  }
-  const int nseg = cdiv(2 * a.H * a.d, 64 * V);
-  const int grid = cdiv((long)a.rows * nseg, 4);
-#define FF_RMS(LPH)                                                            \
-  do {                                                                         \
-    if (dtype == DT_BF16) FF_LAUNCH((k_rms_qk<DT_BF16, LPH>), grid, 256, 0, s, a); \
-    else FF_LAUNCH((k_rms_qk<DT_F32, LPH>), grid, 256, 0, s, a);              \
-  } while (0)
-  if (lph == 8) FF_RMS(8);
-  else if (lph == 16) FF_RMS(16);
-  else FF_RMS(32);
-#undef FF_RMS
+  const int V = dtype == DT_BF16 ? 8 : 4, lph = a.d / V;
+  if (a.d % V || lph < 1 || lph > 64) return hipErrorInvalidValue;
+  // a row per wavefront, split over several where rows alone leave CUs idle
+  const int groups = cdiv(2 * a.H, 64 / lph);
+  const int parts = std::min(groups, std::max(1, cdiv(4096, a.rows)));
+  const int grid = cdiv((long)a.rows * parts, 4);
+  if (dtype == DT_BF16) FF_LAUNCH(k_rms_qk<DT_BF16>, grid, 256, 0, s, a, parts);
+  else FF_LAUNCH(k_rms_qk<DT_F32>, grid, 256, 0, s, a, parts);
   return hipGetLastError();
 }
 

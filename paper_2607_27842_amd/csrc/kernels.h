@@ -111,13 +111,6 @@ struct LnModArgs {
 };
 hipError_t ln_modulate(int dtype, const LnModArgs& a, hipStream_t s);
 
-// In-place per-head RMSNorm of columns [col0, col0 + H*d) of x (model dtype):
-// x_h <- x_h * g / sqrt(mean(x_h^2) + eps) for each row r < rows (physical via map).
-struct RmsArgs {
-  void* x; int ld; RowMap map; int rows, H, d, col0;
-  const void* g; float eps;
-};
-hipError_t rms_heads(int dtype, const RmsArgs& a, hipStream_t s);
 // Rotary embedding applied after the q / k norms: head dims split into chunks of axes[a]
 // (all 0: none); the pair (2i, 2i+1) of chunk a turns by pos_a * theta^(-2i / axes[a]),
 // pos = (0, 0, 0) for rows n < n_txt of a sample, else (frame, row, column) of image row
@@ -126,8 +119,8 @@ struct Rope {
   int axes[3]; float log2_theta;
   int n_txt, Hp, Wp;
 };
-// Both per-head RMSNorms of a qkv row block: q at columns [0, H*d) with gain gq, k at
-// [H*d, 2*H*d) with gain gk (in place), then the rotary embedding of q and k.
+// Both per-head RMSNorms of a qkv row block, in place, x_h <- x_h * g / sqrt(mean(x_h^2) + eps):
+// q at columns [0, H*d) with gain gq, k at [H*d, 2*H*d) with gain gk; then their rotary embedding.
 struct RmsQKArgs {
   void* x; int ld; RowMap map; int rows, H, d;
   const void* gq; const void* gk; float eps;

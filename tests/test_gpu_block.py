@@ -241,6 +241,26 @@ def test_block_gemm_tiles_off_the_64_grid(kind, H, B, lat, n_txt):
     check_block(cfg, W, seed=H)
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("kind,d,H,axes", [
+    (synth.MMDIT_DOUBLE, 24, 7, None),            # 3 or 6 lanes a head
+    (synth.MMDIT_DOUBLE, 40, 13, None),           # 5 or 10 lanes, a last group with 2 of its 12 heads
+    (synth.MMDIT_SINGLE, 96, 3, (16, 40, 40)),    # 12 or 24 lanes, rotated
+    (synth.MMDIT_DOUBLE, 128, 5, (16, 56, 56)),   # 16 or 32 lanes, rotated; 10 heads in groups of 4 or 2
+    # one or two lanes a head.  (C = 264: at C = 8, one head, the update is about 0.015 at most, and
+    # the rounding of h alone, 2^-24 of |h| <= 4, is 1.6e-5 of it in fp32.)
+    (synth.MMDIT_SINGLE, 8, 33, (4, 2, 2)),
+])
+def test_block_qk_norm_head_dims(dtype, kind, d, H, axes):
+    """q/k norm and rotation for head dims whose lanes do and do not divide a wavefront."""
+    need_gpu()
+    cfg = ragged_cfg(kind, dtype, d=d, H=H, n_txt=13, lat=(4, 2, 14, 10))
+    if axes:
+        cfg["rope_axes"], cfg["rope_theta"] = axes, 10000.0
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.2), kind)
+    check_block(cfg, W, seed=d)
+
+
 @pytest.mark.parametrize("kind,H,B,lat,n_txt", [
     (synth.DIT, 33, 1, (4, 1, 22, 60), 0),              # M = 330, K = 264 (five stages: the least for 64x64) / 528: 64x64, 64x32
     (synth.DIT, 49, 3, (4, 1, 40, 50), 0),              # M = 1500, K = 392 / 784: 128x64, 64x64, 64x96
