@@ -169,66 +169,88 @@ __global__ __launch_bounds__(256) void k_ln_modulate(LnModArgs a) {
 // q and k heads of a row: each lane owns one 16-byte chunk of a head (lph = d / V lanes a head,
 // hw = 64 / lph heads a wavefront at a time), the lanes of a head add their sums of squares with
 // shuffles (fixed order), and every lane rescales its own chunk.  A wavefront takes every
-// parts-th group of hw heads of its row, four groups' loads at a time.  A lane's chunk has the
-// same place in each of its heads, so the rotation's angles, sines and cosines are formed once
-// per row and lane: the kernel is bound by memory where it was bound by sincosf when it formed
-// them per head.
-template <int DT>
+// parts-th group of hw heads of its row, UN of them at a time.
+// Bound by memory, on few rows by latency.  Without rotation, and with it on few rows, a
+// wavefront takes one group (UN = 1, parts = groups).  With rotation on many rows it walks them
+// (UN = 4): a lane's chunk has the same place in each of its heads, so the angles, sines and cosines
+// are formed once per row and lane, not per head (bound by sincosf then).  Either way the loads of
+// the first groups are in flight while the angles are formed.
+// Mean of this launch and the LayerNorm before it (single block, H = 24, bf16), against a kernel of
+// one group a wavefront that formed the angles per head: d = 128, N = 4608 without rotation 14.9 -> 14.4
+// us (16.6 when these rows are walked too), rotated 23.5 -> 16.3; N = 1536 rotated 8.8 -> 7.5; N = 320
+// rotated 4.4 -> 4.9, at d = 64 4.2 -> 4.2 (5.8 and 4.6 when those rows are walked).
+// LPH: lanes a head, or 0 to take it from the arguments (shuffles of any width).
+template <int DT, int LPH, bool ROT, int UN>
 __global__ __launch_bounds__(256) void k_rms_qk(RmsQKArgs a, int parts) {
   using S = St<DT>;
-  constexpr int V = S::V, UN = 4;
+  constexpr int V = S::V;
   const int lane = threadIdx.x & 63;
-  const long wv = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const long r = wv / parts;
-  if (r >= a.rows) return;                        // whole wavefront, no barrier below
-  const int part = (int)(wv % parts);
-  const int lph = a.d / V, hw = 64 / lph, sub = lane / lph, e = lane % lph * V, groups = (2 * a.H + hw - 1) / hw;
-  const bool pow2 = (lph & (lph - 1)) == 0;
-  const size_t base = (size_t)a.map.phys((int)r) * a.ld + e;
-  float gq[V], gk[V], sn[V / 2], cs[V / 2];
-  if ((((uintptr_t)a.gq | (uintptr_t)a.gk) & 15) == 0) {
-    S::load(a.gq, e, gq);
-    S::load(a.gk, e, gk);
-  } else {
+  const uint32_t wv = blockIdx.x * 4u + (threadIdx.x >> 6);   // rows * parts < 2^32 (host check)
+  const uint32_t row = wv / (uint32_t)parts;
+  if (row >= (uint32_t)a.rows) return;            // whole wavefront, no barrier below
+  const int r = (int)row, part = (int)(wv - row * (uint32_t)parts);
+  const int lph = LPH ? LPH : a.d / V, hw = 64 / lph, sub = lane / lph, e = lane % lph * V;
+  const int groups = (2 * a.H + hw - 1) / hw;
+  const size_t base = (size_t)a.map.phys(r) * a.ld + e;
+  const bool wide = (((uintptr_t)a.gq | (uintptr_t)a.gk) & 15) == 0;
+  auto gain = [&](const void* g, float* v) __attribute__((always_inline)) {
+    if (wide) {
+      S::load(g, e, v);
+    } else {
 #pragma unroll
-    for (int j = 0; j < V; ++j) { gq[j] = S::ld1(a.gq, e + j); gk[j] = S::ld1(a.gk, e + j); }
-  }
-  const Rope& ro = a.rope;
-  // the row's token n within its sample; image rows carry (frame, row, column) ids
-  const int n = a.map.off + (int)(r % a.map.n_seg);
-  const bool turn = ro.axes[0] + ro.axes[1] + ro.axes[2] && n >= ro.n_txt;
-  if (turn) {
-    const int t = n - ro.n_txt;
-    const float pos[3] = {(float)(t / (ro.Hp * ro.Wp)), (float)((t / ro.Wp) % ro.Hp), (float)(t % ro.Wp)};
-#pragma unroll
-    for (int j = 0; j < V; j += 2) {   // e + j is even: a lane holds whole pairs
-      int p = e + j, ax = 0;
-      if (p >= ro.axes[0]) { p -= ro.axes[0]; ax = 1; if (p >= ro.axes[1]) { p -= ro.axes[1]; ax = 2; } }
-      // selects, not ro.axes[ax] / pos[ax]: a lane-varying index into the argument block
-      // became a memory load (and a wait) per pair
-      const int da = ax == 0 ? ro.axes[0] : (ax == 1 ? ro.axes[1] : ro.axes[2]);
-      const float ps = ax == 0 ? pos[0] : (ax == 1 ? pos[1] : pos[2]);
-      const float w = exp2f(-(float)p / (float)da * ro.log2_theta);   // theta^(-2i/da), p = 2i
-      sincosf(ps * w, &sn[j / 2], &cs[j / 2]);
+      for (int j = 0; j < V; ++j) v[j] = S::ld1(g, e + j);
     }
-  }
-  for (int g0 = part; g0 < groups; g0 += UN * parts) {
-    float v[UN][V];
-    bool on[UN];
+  };
+  float v[UN][V], gq[V], gk[V], sn[V / 2], cs[V / 2];
+  bool on[UN];
+  auto request = [&](int g0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const int h = (g0 + u * parts) * hw + sub;
       on[u] = sub < hw && h < 2 * a.H;
       S::load(a.x, base + (size_t)(on[u] ? h : 0) * a.d, v[u]);
     }
+  };
+  request(part);
+  if (UN > 1) {
+    gain(a.gq, gq);
+    gain(a.gk, gk);
+  } else {
+    gain(part * hw + sub < a.H ? a.gq : a.gk, gq);
+  }
+  bool turn = false;
+  if constexpr (ROT) {
+    const Rope& ro = a.rope;
+    // the row's token n within its sample; image rows carry (frame, row, column) ids
+    const int n = a.map.off + r % a.map.n_seg;
+    turn = n >= ro.n_txt;
+    if (turn) {
+      const int t = n - ro.n_txt;
+      const float pos[3] = {(float)(t / (ro.Hp * ro.Wp)), (float)((t / ro.Wp) % ro.Hp), (float)(t % ro.Wp)};
+#pragma unroll
+      for (int j = 0; j < V; j += 2) {   // e + j is even: a lane holds whole pairs
+        int p = e + j, ax = 0;
+        if (p >= ro.axes[0]) { p -= ro.axes[0]; ax = 1; if (p >= ro.axes[1]) { p -= ro.axes[1]; ax = 2; } }
+        // selects, not ro.axes[ax] / pos[ax]: a lane-varying index into the argument block
+        // became a memory load (and a wait) per pair
+        const int da = ax == 0 ? ro.axes[0] : (ax == 1 ? ro.axes[1] : ro.axes[2]);
+        const float ps = ax == 0 ? pos[0] : (ax == 1 ? pos[1] : pos[2]);
+        const float w = exp2f(-(float)p / (float)da * ro.log2_theta);   // theta^(-2i/da), p = 2i
+        sincosf(ps * w, &sn[j / 2], &cs[j / 2]);
+      }
+    }
+  }
+  for (int g0 = part;;) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const int h = (g0 + u * parts) * hw + sub;
       float ss = 0.f;
 #pragma unroll
       for (int j = 0; j < V; ++j) ss = fmaf(v[u][j], v[u][j], ss);
-      if (pow2) {
-        for (int o = lph / 2; o >= 1; o /= 2) ss += __shfl_xor(ss, o, 64);
+      if (LPH || (lph & (lph - 1)) == 0) {
+#pragma unroll
+        for (int o = (LPH ? LPH : 64) / 2; o >= 1; o /= 2)
+          if (LPH || o < lph) ss += __shfl_xor(ss, o, 64);
       } else {
         float sum = 0.f;
         for (int i = 0; i < lph; ++i) sum += __shfl(ss, (sub * lph + i) & 63, 64);
@@ -237,7 +259,7 @@ __global__ __launch_bounds__(256) void k_rms_qk(RmsQKArgs a, int parts) {
       if (!on[u]) continue;
       const float inv = 1.0f / sqrtf(ss / (float)a.d + a.eps);
 #pragma unroll
-      for (int j = 0; j < V; ++j) v[u][j] = v[u][j] * inv * (h < a.H ? gq[j] : gk[j]);
+      for (int j = 0; j < V; ++j) v[u][j] = v[u][j] * inv * (UN == 1 || h < a.H ? gq[j] : gk[j]);
       if (turn) {
 #pragma unroll
         for (int j = 0; j < V; j += 2) {
@@ -248,6 +270,10 @@ __global__ __launch_bounds__(256) void k_rms_qk(RmsQKArgs a, int parts) {
       }
       S::store(a.x, base + (size_t)h * a.d, v[u]);
     }
+    if (UN == 1) break;   // parts = groups
+    g0 += UN * parts;
+    if (g0 >= groups) break;
+    request(g0);
   }
 }
 
@@ -898,17 +924,35 @@ hipError_t ln_modulate(int dtype, const LnModArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int DT, int LPH>
+void launch_rms(const RmsQKArgs& a, bool rot, bool walk, int grid, int parts, hipStream_t s) {
+  if (!rot) FF_LAUNCH((k_rms_qk<DT, LPH, false, 1>), grid, 256, 0, s, a, parts);
+  else if (walk) FF_LAUNCH((k_rms_qk<DT, LPH, true, 4>), grid, 256, 0, s, a, parts);
+  else FF_LAUNCH((k_rms_qk<DT, LPH, true, 1>), grid, 256, 0, s, a, parts);
+}
+template <int DT>
+hipError_t launch_rms(const RmsQKArgs& a, hipStream_t s) {
+  const int lph = a.d / St<DT>::V;
+  if (a.d % St<DT>::V || lph < 1 || lph > 64) return hipErrorInvalidValue;
+  const int groups = cdiv(2 * a.H, 64 / lph);
+  const bool rot = a.rope.axes[0] + a.rope.axes[1] + a.rope.axes[2] != 0;
+  // rotated rows are walked, split over several wavefronts where rows alone leave CUs idle, until
+  // each would take one group
+  const int split = std::max(1, cdiv(4096, a.rows));
+  const bool walk = rot && split < groups;
+  const int parts = walk ? split : groups;
+  if ((uint64_t)a.rows * parts > 0xfffffff0ull) return hipErrorInvalidValue;
+  const int grid = cdiv((long)a.rows * parts, 4);
+  if (lph == 8) launch_rms<DT, 8>(a, rot, walk, grid, parts, s);
+  else if (lph == 16) launch_rms<DT, 16>(a, rot, walk, grid, parts, s);
+  else if (lph == 32) launch_rms<DT, 32>(a, rot, walk, grid, parts, s);
+  else launch_rms<DT, 0>(a, rot, walk, grid, parts, s);
+  return hipGetLastError();
+}
+
 hipError_t rms_qk(int dtype, const RmsQKArgs& a, hipStream_t s) {
   if (a.rows == 0) return hipSuccess;
-  const int V = dtype == DT_BF16 ? 8 : 4, lph = a.d / V;
-  if (a.d % V || lph < 1 || lph > 64) return hipErrorInvalidValue;
-  // a row per wavefront, split over several where rows alone leave CUs idle
-  const int groups = cdiv(2 * a.H, 64 / lph);
-  const int parts = std::min(groups, std::max(1, cdiv(4096, a.rows)));
-  const int grid = cdiv((long)a.rows * parts, 4);
-  if (dtype == DT_BF16) FF_LAUNCH(k_rms_qk<DT_BF16>, grid, 256, 0, s, a, parts);
-  else FF_LAUNCH(k_rms_qk<DT_F32>, grid, 256, 0, s, a, parts);
-  return hipGetLastError();
+  return dtype == DT_BF16 ? launch_rms<DT_BF16>(a, s) : launch_rms<DT_F32>(a, s);
 }
 
 hipError_t gemv(int dtype, const GemvArgs& a, hipStream_t s) {

@@ -261,6 +261,22 @@ def test_block_qk_norm_head_dims(dtype, kind, d, H, axes):
     check_block(cfg, W, seed=d)
 
 
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("kind,d,H,axes", [
+    (synth.MMDIT_DOUBLE, 40, 37, (8, 16, 16)),    # 7 or 13 groups of heads a row
+    (synth.MMDIT_SINGLE, 64, 24, (16, 24, 24)),   # 6 or 12
+    (synth.MMDIT_DOUBLE, 128, 12, (16, 56, 56)),  # 6 or 12
+])
+def test_block_qk_norm_rotated_rows_walked(dtype, kind, d, H, axes):
+    """Rotated q and k with enough rows that a wavefront walks the groups of a row (1440 image
+    rows: three wavefronts a row), several groups' loads at a time and, in fp32, a second turn."""
+    need_gpu()
+    cfg = ragged_cfg(kind, dtype, d=d, H=H, n_txt=13, lat=(4, 2, 40, 36), mlp_ratio=1)
+    cfg["rope_axes"], cfg["rope_theta"] = axes, 10000.0
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.2), kind)
+    check_block(cfg, W, seed=d, rows=np.array([0, 12, 13, 14, 31, 200, 372, 373, 500, 731, 732]))
+
+
 @pytest.mark.parametrize("kind,H,B,lat,n_txt", [
     (synth.DIT, 33, 1, (4, 1, 22, 60), 0),              # M = 330, K = 264 (five stages: the least for 64x64) / 528: 64x64, 64x32
     (synth.DIT, 49, 3, (4, 1, 40, 50), 0),              # M = 1500, K = 392 / 784: 128x64, 64x64, 64x96
