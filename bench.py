@@ -45,7 +45,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_gemm_dit_xl2.json")
 # (ff_ctx_hist_sums); --no-hist-sums drafts layer by layer
 HIST_SUMS = True
 COND_CACHE = True   # conditioning of the whole schedule formed at step 0 (ff_ctx_cond_cache)
-GEMM_SOURCES = [os.path.join(ROOT, "paper_2607_27842_amd", "csrc", f) for f in ("k_gemm.hip", "dev_common.h")]
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2607_27842_amd", "csrc", f) for f in ("k_gemm.hip", "dev_common.h", "gemm_plan.h")]
 
 
 def log(*a):

@@ -1,0 +1,88 @@
+// Host side of the bf16 GEMM launches: which output tile a problem (or two in one launch) takes.
+// Plain arithmetic on the shapes, without HIP.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+
+namespace ff {
+
+// M x N outputs over K; operand rows lda and ldw elements apart.  Row r of A is row
+// r % seg of sample r / seg, samples `rows` rows apart (seg == rows: consecutive).
+struct GemmShape { int M, N, K, lda, ldw, seg, rows; };
+
+// Tile choice: the candidate with the least estimated time.  A round of workgroups takes
+// lat + k * K us, bound by its own chain of stages, and 256-row tiles keep the whole card busy for
+// pow us per 256 tiles and unit of K when the card's power limit binds (large grids: the clock
+// falls to about 1.6 GHz, so that a grid that leaves CUs idle runs its tiles faster); the smaller
+// tiles' pow is their share of the L2 at long K (1536 x 3072 x 15360: 128x96 223 us, 128x192 174).  Tiles that
+// leave room for a second workgroup per CU take lat2 + k2 * K for a round of 257 to 512.
+// Measured on MI355X with random bf16 data; 256-row tiles run k_gemm_pp, the others k_gemm_ks.
+// In us at K = 1152 / 4608 for one round of few tiles: 256x256 31 / 85, 256x192 28 / 70, 256x128
+// 21 / 57-69, 128x192 19 / 58, 128x128 15 / 33, 128x96 13.6 / 30, 128x64 9.3 / 22.5, 64x96 8.1 / 19,
+// 64x64 7.0 / 15.6 (288 tiles: 10.3 / 26.7), 64x32 6.1 / 12.9 (288: 8.2 / 20.5), 64x96 with 384 tiles 14.5 / 37; a full round at K =
+// 3072 (clock down): 77, 62, 47 us for the 256-row tiles.
+// What the 256-row tiles take against the kernels before them (256x256 and 256x192 of 32x32x16
+// MFMAs with one wait and barrier per stage): M = 4608, N = 21504, K = 3072 545 -> 460 us
+// (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us, 14310 x 8192 x 2048 440 -> 370 us.
+enum { kTile256, kTile256x192, kTile256x128, kTile128x192, kTile128, kTile128x96, kTile128x64, kTile64x96, kTile64,
+       kTile64x32, kTileCount };
+constexpr int ks_nst(int tile) { return tile == kTile128 || tile == kTile64 ? 5 : tile == kTile64x32 ? 6 : 4; }
+struct TilePlan { int tile; double cost; };
+struct TileCost { int bm, bn; double lat, k, pow, lat2, k2; };
+constexpr TileCost kTileCost[kTileCount] = {
+    {256, 256, 15.0, 0.0150, 0.0245, 0, 0},  {256, 192, 13.0, 0.0122, 0.0192, 0, 0},
+    {256, 128, 7.5, 0.0118, 0.0145, 0, 0},   {128, 192, 8.0, 0.0108, 0, 0, 0},
+    {128, 128, 8.0, 0.0058, 0.0140, 0, 0},   {128, 96, 8.0, 0.0048, 0.0095, 0, 0},
+    {128, 64, 4.8, 0.0039, 0.0095, 0, 0},         {64, 96, 4.6, 0.0032, 0.0045, 6.5, 0.0062},
+    {64, 64, 4.2, 0.0025, 0.0048, 5.0, 0.0047}, {64, 32, 3.9, 0.0020, 0.0028, 4.0, 0.0036}};
+
+inline long tiles_of(const GemmShape* a, int n, int bm, int bn) {
+  long t = 0;
+  for (int i = 0; i < n; ++i) t += (long)((a[i].M + bm - 1) / bm) * ((a[i].N + bn - 1) / bn);
+  return t;
+}
+
+// The operand rows of every bm x bn tile lie within a 32-bit byte offset of its first row (bm
+// consecutive rows of a row map span at most (bm - 1) / seg + 1 further samples, and no more than
+// there are), with room left for the offset along K.
+inline bool dma_ok(const GemmShape* a, int n, int bm, int bn) {
+  for (int i = 0; i < n; ++i) {
+    const int more = std::min((bm - 1) / a[i].seg + 1, (a[i].M - 1) / a[i].seg);
+    const uint64_t span = a[i].seg == a[i].rows ? bm : (uint64_t)more * a[i].rows + bm;
+    if (span * a[i].lda * 2 > 0xf0000000ull || (uint64_t)bn * a[i].ldw * 2 > 0xf0000000ull) return false;
+  }
+  return true;
+}
+
+// n (1 or 2) problems in one launch, each with rows and columns; tile -1: none fits
+inline TilePlan plan_tiles(const GemmShape* a, int n) {
+  TilePlan best{-1, 1e300};
+  int K = 0, nk = 1 << 30;
+  for (int i = 0; i < n; ++i) {
+    K = std::max(K, a[i].K);
+    nk = std::min(nk, (a[i].K + 63) / 64);
+  }
+  for (int c = 0; c < kTileCount; ++c) {
+    if (nk < (c <= kTile256x128 ? 3 : ks_nst(c))) continue;   // the stages that the kernel's prologue takes
+    const TileCost& t = kTileCost[c];
+    if (!dma_ok(a, n, t.bm, t.bn)) continue;
+    const long tiles = tiles_of(a, n, t.bm, t.bn), slots = t.lat2 > 0 ? 512 : 256, rest = tiles % slots;
+    const double one = t.lat + t.k * K, full = t.lat2 > 0 ? t.lat2 + t.k2 * K : one;
+    const double cost = std::max(tiles / slots * full + (rest == 0 ? 0 : rest <= 256 ? one : full), tiles / 256.0 * t.pow * K);
+    if (cost < best.cost) best = TilePlan{c, cost};
+  }
+  return best;
+}
+
+// Two problems share a launch when that is estimated to take no longer than two launches: the same
+// tile for both must exist, or neither has any of its own (a problem that the DMA tiles
+// cannot take keeps the other one from nothing).
+inline bool plan_grouped(const GemmShape& a0, const GemmShape& a1) {
+  const GemmShape both[2] = {a0, a1};
+  const TilePlan b = plan_tiles(both, 2), p0 = plan_tiles(&a0, 1), p1 = plan_tiles(&a1, 1);
+  if (b.tile < 0) return p0.tile < 0 && p1.tile < 0;
+  return b.cost <= p0.cost + p1.cost;
+}
+
+}  // namespace ff

@@ -4,10 +4,10 @@
 // bf16: 256-row workgroup tiles of v_mfma_f32_16x16x32_bf16 (k_gemm_pp) where the grid fills
 // the card, 64- and 128-row tiles of v_mfma_f32_32x32x16_bf16 whose waves split K (k_gemm_ks) on
 // small grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
-// rows, double buffer) covers K <= 128 off the 64 grid (the patch embedding).
+// rows, double buffer) takes what they cannot: fewer stages than they need, operand rows too far apart.
 // fp32: fp32 MFMAs on 16x16, 32x32 or 64x64 tiles, the waves of a tile splitting K.
-#include <algorithm>
 #include "dev_common.h"
+#include "gemm_plan.h"
 
 namespace ff {
 
@@ -1065,72 +1065,12 @@ void launch_ks(const GemmArgs* a, int n, hipStream_t s) {
   }
 }
 
-// Tile choice: the candidate with the least estimated time.  A round of workgroups takes
-// lat + k * K us, bound by its own chain of stages, and 256-row tiles keep the whole card busy for
-// pow us per 256 tiles and unit of K when the card's power limit binds (large grids: the clock
-// falls to about 1.6 GHz, so that a grid that leaves CUs idle runs its tiles faster); the smaller
-// tiles' pow is their share of the L2 at long K (1536 x 3072 x 15360: 128x96 223 us, 128x192 174).  Tiles that
-// leave room for a second workgroup per CU take lat2 + k2 * K for a round of 257 to 512.
-// Measured on MI355X with random bf16 data; 256-row tiles run k_gemm_pp, the others k_gemm_ks.
-// In us at K = 1152 / 4608 for one round of few tiles: 256x256 31 / 85, 256x192 28 / 70, 256x128
-// 21 / 57-69, 128x192 19 / 58, 128x128 15 / 33, 128x96 13.6 / 30, 128x64 9.3 / 22.5, 64x96 8.1 / 19,
-// 64x64 7.0 / 15.6 (288 tiles: 10.3 / 26.7), 64x32 6.1 / 12.9 (288: 8.2 / 20.5), 64x96 with 384 tiles 14.5 / 37; a full round at K =
-// 3072 (clock down): 77, 62, 47 us for the 256-row tiles.
-// What the 256-row tiles take against the kernels before them (256x256 and 256x192 of 32x32x16
-// MFMAs with one wait and barrier per stage): M = 4608, N = 21504, K = 3072 545 -> 460 us
-// (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us, 14310 x 8192 x 2048 440 -> 370 us.
-enum { kTile256, kTile256x192, kTile256x128, kTile128x192, kTile128, kTile128x96, kTile128x64, kTile64x96, kTile64,
-       kTile64x32, kTileCount };
-constexpr int ks_nst(int tile) { return tile == kTile128 || tile == kTile64 ? 5 : tile == kTile64x32 ? 6 : 4; }
-struct TilePlan { int tile; double cost; };
-struct TileCost { int bm, bn; double lat, k, pow, lat2, k2; };
-constexpr TileCost kTileCost[kTileCount] = {
-    {256, 256, 15.0, 0.0150, 0.0245, 0, 0},  {256, 192, 13.0, 0.0122, 0.0192, 0, 0},
-    {256, 128, 7.5, 0.0118, 0.0145, 0, 0},   {128, 192, 8.0, 0.0108, 0, 0, 0},
-    {128, 128, 8.0, 0.0058, 0.0140, 0, 0},   {128, 96, 8.0, 0.0048, 0.0095, 0, 0},
-    {128, 64, 4.8, 0.0039, 0.0095, 0, 0},         {64, 96, 4.6, 0.0032, 0.0045, 6.5, 0.0062},
-    {64, 64, 4.2, 0.0025, 0.0048, 5.0, 0.0047}, {64, 32, 3.9, 0.0020, 0.0028, 4.0, 0.0036}};
-
-long tiles_of(const GemmArgs* a, int n, int bm, int bn) {
-  long t = 0;
-  for (int i = 0; i < n; ++i) t += (long)((a[i].M + bm - 1) / bm) * ((a[i].N + bn - 1) / bn);
-  return t;
-}
-
-// Operand rows lie within a 32-bit byte offset of their tile's first row (256 consecutive rows
-// of a row map span at most 255 / n_seg + 1 further samples, and no more than there are).
-bool dma_ok(const GemmArgs* a, int n) {
-  for (int i = 0; i < n; ++i) {
-    const RowMap& m = a[i].amap;
-    const int more = std::min(255 / m.n_seg + 1, (a[i].M - 1) / m.n_seg);
-    const uint64_t span = m.n_seg == m.N ? 256 : (uint64_t)more * m.N + 256;
-    if (span * a[i].lda * 2 > 0xf0000000ull || 256ull * a[i].ldw * 2 > 0xf0000000ull) return false;
-  }
-  return true;
-}
-
-TilePlan plan_tiles(const GemmArgs* a, int n) {
-  TilePlan best{-1, 1e300};
-  if (!dma_ok(a, n)) return best;
-  int K = 0, nk = 1 << 30;
-  for (int i = 0; i < n; ++i) {
-    K = std::max(K, a[i].K);
-    nk = std::min(nk, (a[i].K + 63) / 64);
-  }
-  for (int c = 0; c < kTileCount; ++c) {
-    if (nk < (c <= kTile256x128 ? 3 : ks_nst(c))) continue;   // the stages that the kernel's prologue takes
-    const TileCost& t = kTileCost[c];
-    const long tiles = tiles_of(a, n, t.bm, t.bn), slots = t.lat2 > 0 ? 512 : 256, rest = tiles % slots;
-    const double one = t.lat + t.k * K, full = t.lat2 > 0 ? t.lat2 + t.k2 * K : one;
-    const double cost = std::max(tiles / slots * full + (rest == 0 ? 0 : rest <= 256 ? one : full), tiles / 256.0 * t.pow * K);
-    if (cost < best.cost) best = TilePlan{c, cost};
-  }
-  return best;
-}
+GemmShape shape_of(const GemmArgs& a) { return GemmShape{a.M, a.N, a.K, a.lda, a.ldw, a.amap.n_seg, a.amap.N}; }
 
 template <int EPI, bool OF, bool RF>
 void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
-  switch (plan_tiles(a, n).tile) {
+  const GemmShape sh[2] = {shape_of(a[0]), shape_of(a[n - 1])};
+  switch (plan_tiles(sh, n).tile) {
     case kTile256: launch_pp<4, EPI, OF, RF>(a, n, s); break;
     case kTile256x192: launch_pp<3, EPI, OF, RF>(a, n, s); break;
     case kTile256x128: launch_pp<2, EPI, OF, RF>(a, n, s); break;
@@ -1141,7 +1081,7 @@ void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
     case kTile64x96: launch_ks<64, 96, ks_nst(kTile64x96), EPI, OF, RF>(a, n, s); break;
     case kTile64: launch_ks<64, 64, ks_nst(kTile64), EPI, OF, RF>(a, n, s); break;
     case kTile64x32: launch_ks<64, 32, ks_nst(kTile64x32), EPI, OF, RF>(a, n, s); break;
-    default: launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s); break;   // K <= 128 off the 64 grid
+    default: launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s); break;
   }
 }
 
@@ -1195,14 +1135,11 @@ hipError_t gemm2(int dtype, const GemmArgs& a0, const GemmArgs& a1, hipStream_t 
   const bool e0 = a0.M > 0 && a0.N > 0, e1 = a1.M > 0 && a1.N > 0;
   const bool ungated = a0.epi != EPI_GATED && a1.epi != EPI_GATED;
   const bool same = (a0.epi == a1.epi || ungated) && a0.out_f32 == a1.out_f32 && a0.resid_f32 == a1.resid_f32;
-  // Grouping pays when the combined launch is estimated to take no longer than the two.
-  const GemmArgs both[2] = {a0, a1};
-  const TilePlan pb = plan_tiles(both, 2);
-  const bool pays = pb.tile < 0 || pb.cost <= plan_tiles(&a0, 1).cost + plan_tiles(&a1, 1).cost;
-  if (dtype == DT_F32 || !same || !e0 || !e1 || !pays) {
+  if (dtype == DT_F32 || !same || !e0 || !e1 || !plan_grouped(shape_of(a0), shape_of(a1))) {
     hipError_t e = gemm(dtype, a0, s);
     return e != hipSuccess ? e : gemm(dtype, a1, s);
   }
+  const GemmArgs both[2] = {a0, a1};
   return gemm_bf16(both, 2, s);
 }
 

@@ -49,8 +49,9 @@ struct GemmArgs {
 };
 hipError_t gemm(int dtype, const GemmArgs& a, hipStream_t s);
 // Two GEMMs in one launch (bf16) when they share out_f32 and resid_f32 and either share epi
-// or mix EPI_BIAS with EPI_BIAS_GELU, and when the combined grid does not take more rounds
-// over the CUs; otherwise two launches.  Same results as two gemm() calls.
+// or mix EPI_BIAS with EPI_BIAS_GELU, and when that is estimated to take no longer than two
+// launches; otherwise two launches.  The results are those of two gemm() calls up to the order of
+// the sums over K, which depends on the tile.
 hipError_t gemm2(int dtype, const GemmArgs& a0, const GemmArgs& a1, hipStream_t s);
 
 // y[b, n] = (add ? add[b*ldadd + n] : 0) + act( sum_k f(x[b*ldx + k]) * W[n, k] + bias[n] )

@@ -1,0 +1,73 @@
+"""The host-side choice of the bf16 GEMM tiles (csrc/gemm_plan.h, plain C++), compiled with g++ and
+called from tests: which tile each GEMM of an exact block takes, and which of them share a launch."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+import synth
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_27842_amd", "csrc")
+SRC = r"""
+#include "gemm_plan.h"
+static ff::GemmShape shape(const int* v) { return {v[0], v[1], v[2], v[3], v[4], v[5], v[6]}; }
+extern "C" int tile(const int* a, const int* b) {
+  const ff::GemmShape s[2] = {shape(a), shape(b ? b : a)};
+  return ff::plan_tiles(s, b ? 2 : 1).tile;
+}
+static_assert(ff::kTileCount == 10, "TILES below");
+extern "C" int grouped(const int* a, const int* b) { return ff::plan_grouped(shape(a), shape(b)); }
+"""
+
+# in the order of the enum; -1 (the last) is the register-staged kernel
+TILES = ("256x256", "256x192", "256x128", "128x192", "128x128", "128x96", "128x64", "64x96", "64x64", "64x32", "reg")
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
+        with open(src, "w") as f:
+            f.write(SRC)
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, src, "-o", so], check=True)
+        return ctypes.CDLL(so)
+
+
+def shape(M, N, K, lda=None, ldw=None, seg=None, rows=None):
+    """A problem: M x N over K; row r of A is row r % seg of sample r / seg, samples `rows` rows apart."""
+    seg = M if seg is None else seg
+    return (ctypes.c_int * 7)(M, N, K, K if lda is None else lda, K if ldw is None else ldw, seg,
+                              seg if rows is None else rows)
+
+
+def tile(a, b=None):
+    """The tile that problem a, or a and b in one launch, take."""
+    return TILES[_lib().tile(a, b)]
+
+
+def grouped(a, b):
+    return bool(_lib().grouped(a, b))
+
+
+def block_tiles(cfg):
+    """The launches of one exact block of cfg (bf16), in order: "gemm tile", or "gemm tile x2" for two
+    problems in one launch."""
+    kind, C, M, B, nt = cfg["kinds"][0], cfg["C"], cfg["mlp"], cfg["B"], cfg["n_txt"]
+    N = cfg["n_img"] + nt
+    out = []
+
+    def put(name, probs):
+        if len(probs) == 2 and grouped(*probs):
+            out.append("%s %s x2" % (name, tile(*probs)))
+        else:
+            out.extend("%s %s" % (name, tile(p)) for p in probs)
+
+    if kind == synth.MMDIT_SINGLE:
+        put("lin1", [shape(B * N, 3 * C, C, seg=N), shape(B * N, M, C, seg=N)])
+        put("lin2", [shape(B * N, C, C + M, seg=N)])
+        return out
+    segs = [(nt, N), (N - nt, N)] if kind == synth.MMDIT_DOUBLE and nt else [(N - nt, N)]
+    for name, n, k in (("qkv", 3 * C, C), ("proj", C, C), ("fc1", M, C), ("fc2", C, M)):
+        put(name, [shape(B * s, n, k, seg=s, rows=r) for s, r in segs])
+    return out
