@@ -138,12 +138,6 @@ inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 #define FF_AS3(p) ((__attribute__((address_space(3))) void*)(p))
 #define FF_TIE(x) asm volatile("" : "+v"(x))
 
-__device__ __forceinline__ bf16x8_t lds_rd128(const uint16_t* p) {
-  u32x4_t v;
-  const uint32_t off = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)p);
-  asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(off) : "memory");
-  return __builtin_bit_cast(bf16x8_t, v);
-}
 template <int OFF>
 __device__ __forceinline__ bf16x8_t lds_rd128_at(uint32_t addr) {
   static_assert(OFF >= 0 && OFF < 65536, "LDS immediate offset");

@@ -1029,41 +1029,34 @@ GemmGroup<NP> make_group(const GemmArgs* a, int& nwg) {
   return G;
 }
 
-template <int BM, int BN, int WM, int WN, int EPI, bool OF, bool RF>
-void launch_tile(const GemmArgs* a, int n, hipStream_t s) {
-  int nwg;
-  if (n == 1) {
-    const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_bf16<BM, BN, WM, WN, EPI, OF, RF, 1>), nwg, (BM / WM) * (BN / WN) * 64, 0, s, G);
-  } else {
-    const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_bf16<BM, BN, WM, WN, EPI, OF, RF, 2>), nwg, (BM / WM) * (BN / WN) * 64, 0, s, G);
-  }
-}
+// What the two streams of a block, or the two parts of a single block's first projection, share
+constexpr bool grouped_epi(int epi, bool of, bool rf) { return epi == EPI_GATED ? of != rf : !of && !rf; }
+
+// One problem, or two (only those pairs that the path groups are built)
+#define FF_LAUNCH_GEMM(BM, BN, THREADS, ...)                                       \
+  do {                                                                             \
+    int nwg;                                                                       \
+    if (n == 1) {                                                                  \
+      if constexpr (EPI != EPI_BIAS_OR_GELU) {                                     \
+        const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);                      \
+        FF_LAUNCH((__VA_ARGS__, EPI, OF, RF, 1>), nwg, THREADS, 0, s, G);          \
+      }                                                                            \
+    } else {                                                                       \
+      if constexpr (grouped_epi(EPI, OF, RF)) {                                    \
+        const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);                      \
+        FF_LAUNCH((__VA_ARGS__, EPI, OF, RF, 2>), nwg, THREADS, 0, s, G);          \
+      }                                                                            \
+    }                                                                              \
+  } while (0)
 
 template <int TN, int EPI, bool OF, bool RF>
-void launch_pp(const GemmArgs* a, int n, hipStream_t s) {
-  int nwg;
-  if (n == 1) {
-    const GemmGroup<1> G = make_group<256, 64 * TN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_pp<TN, EPI, OF, RF, 1>), nwg, 512, 0, s, G);
-  } else {
-    const GemmGroup<2> G = make_group<256, 64 * TN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_pp<TN, EPI, OF, RF, 2>), nwg, 512, 0, s, G);
-  }
-}
+void launch_pp(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(256, 64 * TN, 512, k_gemm_pp<TN); }
 
 template <int BM, int BN, int NST, int EPI, bool OF, bool RF>
-void launch_ks(const GemmArgs* a, int n, hipStream_t s) {
-  int nwg;
-  if (n == 1) {
-    const GemmGroup<1> G = make_group<BM, BN, 1>(a, nwg);
-    FF_LAUNCH((k_gemm_ks<BM, BN, NST, EPI, OF, RF, 1>), nwg, 512, 0, s, G);
-  } else {
-    const GemmGroup<2> G = make_group<BM, BN, 2>(a, nwg);
-    FF_LAUNCH((k_gemm_ks<BM, BN, NST, EPI, OF, RF, 2>), nwg, 512, 0, s, G);
-  }
-}
+void launch_ks(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(BM, BN, 512, k_gemm_ks<BM, BN, NST); }
+
+template <int EPI, bool OF, bool RF>
+void launch_reg(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(128, 128, 512, k_gemm_bf16<128, 128, 64, 32); }
 
 GemmShape shape_of(const GemmArgs& a) { return GemmShape{a.M, a.N, a.K, a.lda, a.ldw, a.amap.n_seg, a.amap.N}; }
 
@@ -1081,7 +1074,7 @@ void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
     case kTile64x96: launch_ks<64, 96, ks_nst(kTile64x96), EPI, OF, RF>(a, n, s); break;
     case kTile64: launch_ks<64, 64, ks_nst(kTile64), EPI, OF, RF>(a, n, s); break;
     case kTile64x32: launch_ks<64, 32, ks_nst(kTile64x32), EPI, OF, RF>(a, n, s); break;
-    default: launch_tile<128, 128, 64, 32, EPI, OF, RF>(a, n, s); break;
+    default: launch_reg<EPI, OF, RF>(a, n, s); break;
   }
 }
 
@@ -1092,27 +1085,14 @@ namespace {
 // bf16 dispatch of n (1 or 2) problems that share epilogue, output and residual types
 hipError_t gemm_bf16(const GemmArgs* a, int n, hipStream_t s) {
   const bool of = a[0].out_f32 != 0, rf = a[0].resid_f32 != 0;
-  if (n == 2 && a[0].epi != a[1].epi) {   // bias with bias+GELU (gemm2 admits no other mix)
-    if (of) launch_bf16<EPI_BIAS_OR_GELU, true, false>(a, n, s);
-    else launch_bf16<EPI_BIAS_OR_GELU, false, false>(a, n, s);
-    return hipGetLastError();
-  }
-  switch (a[0].epi) {
-    case EPI_BIAS:
-      if (of) launch_bf16<EPI_BIAS, true, false>(a, n, s);
-      else launch_bf16<EPI_BIAS, false, false>(a, n, s);
-      break;
-    case EPI_BIAS_GELU:
-      if (of) launch_bf16<EPI_BIAS_GELU, true, false>(a, n, s);
-      else launch_bf16<EPI_BIAS_GELU, false, false>(a, n, s);
-      break;
-    default:
-      if (of && rf) launch_bf16<EPI_GATED, true, true>(a, n, s);
-      else if (of) launch_bf16<EPI_GATED, true, false>(a, n, s);
-      else if (rf) launch_bf16<EPI_GATED, false, true>(a, n, s);
-      else launch_bf16<EPI_GATED, false, false>(a, n, s);
-      break;
-  }
+  if (n == 2 && a[0].epi != a[1].epi) launch_bf16<EPI_BIAS_OR_GELU, false, false>(a, n, s);   // bias with bias+GELU
+  else if (a[0].epi == EPI_BIAS && of) launch_bf16<EPI_BIAS, true, false>(a, n, s);
+  else if (a[0].epi == EPI_BIAS) launch_bf16<EPI_BIAS, false, false>(a, n, s);
+  else if (a[0].epi == EPI_BIAS_GELU && !of) launch_bf16<EPI_BIAS_GELU, false, false>(a, n, s);
+  else if (a[0].epi == EPI_GATED && of && !rf) launch_bf16<EPI_GATED, true, false>(a, n, s);
+  else if (a[0].epi == EPI_GATED && !of && rf) launch_bf16<EPI_GATED, false, true>(a, n, s);
+  else if (a[0].epi == EPI_GATED && !of) launch_bf16<EPI_GATED, false, false>(a, n, s);
+  else return hipErrorInvalidValue;   // no part of the path asks for it
   return hipGetLastError();
 }
 
@@ -1135,7 +1115,8 @@ hipError_t gemm2(int dtype, const GemmArgs& a0, const GemmArgs& a1, hipStream_t 
   const bool e0 = a0.M > 0 && a0.N > 0, e1 = a1.M > 0 && a1.N > 0;
   const bool ungated = a0.epi != EPI_GATED && a1.epi != EPI_GATED;
   const bool same = (a0.epi == a1.epi || ungated) && a0.out_f32 == a1.out_f32 && a0.resid_f32 == a1.resid_f32;
-  if (dtype == DT_F32 || !same || !e0 || !e1 || !plan_grouped(shape_of(a0), shape_of(a1))) {
+  const bool built = grouped_epi(a0.epi, a0.out_f32 != 0, a0.resid_f32 != 0);
+  if (dtype == DT_F32 || !same || !built || !e0 || !e1 || !plan_grouped(shape_of(a0), shape_of(a1))) {
     hipError_t e = gemm(dtype, a0, s);
     return e != hipSuccess ? e : gemm(dtype, a1, s);
   }

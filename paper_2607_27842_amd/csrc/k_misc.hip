@@ -19,16 +19,6 @@ template <> __device__ __forceinline__ void ld4<DT_BF16>(const void* p, size_t i
   v[0] = __uint_as_float(w.x << 16); v[1] = __uint_as_float(w.x & 0xffff0000u);
   v[2] = __uint_as_float(w.y << 16); v[3] = __uint_as_float(w.y & 0xffff0000u);
 }
-template <int DT> __device__ __forceinline__ void st4(void* p, size_t i, const float* v);
-template <> __device__ __forceinline__ void st4<DT_F32>(void* p, size_t i, const float* v) {
-  *reinterpret_cast<float4*>(reinterpret_cast<float*>(p) + i) = make_float4(v[0], v[1], v[2], v[3]);
-}
-template <> __device__ __forceinline__ void st4<DT_BF16>(void* p, size_t i, const float* v) {
-  uint2 w;
-  w.x = pack_bf16x2(v[0], v[1]);
-  w.y = pack_bf16x2(v[2], v[3]);
-  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(p) + i) = w;
-}
 
 // LayerNorm rows: at most 16 4-element units per lane, C <= 64 * 16 * 4 = 4096 (host check)
 
