@@ -17,7 +17,9 @@ struct GemmShape { int M, N, K, lda, ldw, seg, rows; };
 // falls to about 1.6 GHz, so that a grid that leaves CUs idle runs its tiles faster); the smaller
 // tiles' pow is their share of the L2 at long K (1536 x 3072 x 15360: 128x96 223 us, 128x192 174).  Tiles that
 // leave room for a second workgroup per CU take lat2 + k2 * K for a round of 257 to 512.
-// Measured on MI355X with random bf16 data; 256-row tiles run k_gemm_pp, the others k_gemm_ks.
+// Measured on MI355X with random bf16 data; 256-row tiles run k_gemm_pp (three stages or more), the
+// others k_gemm_ks (four or more), the register-staged kernel k_gemm_bf16 (any K, and operand rows
+// beyond 32-bit offsets of each other).
 // In us at K = 1152 / 4608 for one round of few tiles: 256x256 31 / 85, 256x192 28 / 70, 256x128
 // 21 / 57-69, 128x192 19 / 58, 128x128 15 / 33, 128x96 13.6 / 30, 128x64 9.3 / 22.5, 64x96 8.1 / 19,
 // 64x64 7.0 / 15.6 (288 tiles: 10.3 / 26.7), 64x32 6.1 / 12.9 (288: 8.2 / 20.5), 64x96 with 384 tiles 14.5 / 37; a full round at K =
@@ -26,8 +28,8 @@ struct GemmShape { int M, N, K, lda, ldw, seg, rows; };
 // MFMAs with one wait and barrier per stage): M = 4608, N = 21504, K = 3072 545 -> 460 us
 // (1324 TFLOP/s), 4096 x 3072 x 12288 263 -> 222 us, 14310 x 8192 x 2048 440 -> 370 us.
 enum { kTile256, kTile256x192, kTile256x128, kTile128x192, kTile128, kTile128x96, kTile128x64, kTile64x96, kTile64,
-       kTile64x32, kTileCount };
-constexpr int ks_nst(int tile) { return tile == kTile128 || tile == kTile64 ? 5 : tile == kTile64x32 ? 6 : 4; }
+       kTile64x32, kTileCount, kTileShort64 = kTileCount, kTileShort64x32, kTileReg };
+constexpr int kShortStages = 3;   // most stages of the short tiles
 struct TilePlan { int tile; double cost; };
 struct TileCost { int bm, bn; double lat, k, pow, lat2, k2; };
 constexpr TileCost kTileCost[kTileCount] = {
@@ -36,6 +38,21 @@ constexpr TileCost kTileCost[kTileCount] = {
     {128, 128, 8.0, 0.0058, 0.0140, 0, 0},   {128, 96, 8.0, 0.0048, 0.0095, 0, 0},
     {128, 64, 4.8, 0.0039, 0.0095, 0, 0},         {64, 96, 4.6, 0.0032, 0.0045, 6.5, 0.0062},
     {64, 64, 4.2, 0.0025, 0.0048, 5.0, 0.0047}, {64, 32, 3.9, 0.0020, 0.0028, 4.0, 0.0036}};
+
+constexpr double kNoCost = 1e300;   // no tile of the table fits: the register-staged kernel
+
+// Short K: lat + k * K us for a small grid, base + tile_us + tile_k * K per 256 tiles for a larger one.
+// Up to three stages the short tiles (every stage has a buffer, so nothing waits for a refill), up
+// to kRegK the register-staged kernel, whose few large tiles store faster than the card runs many
+// small ones.  Measured, us, in brackets in the kernel before all of these: K = 192, M = 512, N = 576
+// 4.5 (64x32), 8.0 (256x128), [5.3]; K = 128, M = 4096, N = 128 gated 5.3 (64x32), 7.7 register-staged, [6.1];
+// K = 128, M = 16384, N = 512 9.9 register-staged, 15.0 (64x64), [11.3]; K = 256, M = 4096, N = 1024 9.1
+// register-staged, 11.7 (128x128), 12.2 (256x128), [10.4].  At K = 320 the other tiles are level with it.
+constexpr int kRegK = 256;
+struct ShortCost { int tile, bm, bn; double lat, k, base, tile_us, tile_k; };
+constexpr ShortCost kShortCost[3] = {{kTileShort64, 64, 64, 4.2, 0.0058, 4.0, 0.80, 0.0035},
+                                     {kTileShort64x32, 64, 32, 3.8, 0.0050, 4.0, 0.56, 0.0016},
+                                     {kTileReg, 128, 128, 4.4, 0.0170, 4.4, 0.50, 0.0135}};
 
 inline long tiles_of(const GemmShape* a, int n, int bm, int bn) {
   long t = 0;
@@ -55,16 +72,21 @@ inline bool dma_ok(const GemmShape* a, int n, int bm, int bn) {
   return true;
 }
 
-// n (1 or 2) problems in one launch, each with rows and columns; tile -1: none fits
+// 64-wide K stages of the problem with the fewest
+inline int min_stages(const GemmShape* a, int n) {
+  int nk = (a[0].K + 63) / 64;
+  for (int i = 1; i < n; ++i) nk = std::min(nk, (a[i].K + 63) / 64);
+  return nk;
+}
+
+// n (1 or 2) problems in one launch, each with rows and columns
 inline TilePlan plan_tiles(const GemmShape* a, int n) {
-  TilePlan best{-1, 1e300};
-  int K = 0, nk = 1 << 30;
-  for (int i = 0; i < n; ++i) {
-    K = std::max(K, a[i].K);
-    nk = std::min(nk, (a[i].K + 63) / 64);
-  }
+  TilePlan best{kTileReg, kNoCost};
+  const int nk = min_stages(a, n);
+  int K = 0;
+  for (int i = 0; i < n; ++i) K = std::max(K, a[i].K);
   for (int c = 0; c < kTileCount; ++c) {
-    if (nk < (c <= kTile256x128 ? 3 : ks_nst(c))) continue;   // the stages that the kernel's prologue takes
+    if (nk < (c <= kTile256x128 ? 3 : c == kTile128 ? 5 : 4)) continue;   // the stages that the kernel's prologue takes
     const TileCost& t = kTileCost[c];
     if (!dma_ok(a, n, t.bm, t.bn)) continue;
     const long tiles = tiles_of(a, n, t.bm, t.bn), slots = t.lat2 > 0 ? 512 : 256, rest = tiles % slots;
@@ -72,17 +94,21 @@ inline TilePlan plan_tiles(const GemmShape* a, int n) {
     const double cost = std::max(tiles / slots * full + (rest == 0 ? 0 : rest <= 256 ? one : full), tiles / 256.0 * t.pow * K);
     if (cost < best.cost) best = TilePlan{c, cost};
   }
+  for (const ShortCost& t : kShortCost) {
+    if (t.tile == kTileReg ? K > kRegK : K > 64 * kShortStages || !dma_ok(a, n, t.bm, t.bn)) continue;
+    const double rounds = tiles_of(a, n, t.bm, t.bn) / 256.0;
+    const double cost = std::max(t.lat + t.k * K, t.base + rounds * (t.tile_us + t.tile_k * K));
+    if (cost < best.cost) best = TilePlan{t.tile, cost};
+  }
   return best;
 }
 
-// Two problems share a launch when that is estimated to take no longer than two launches: the same
-// tile for both must exist, or neither has any of its own (a problem that the DMA tiles
-// cannot take keeps the other one from nothing).
+// Two problems share a launch when that is estimated to take no longer than two launches.  Where one
+// of them fits no tile, the other keeps its own.
 inline bool plan_grouped(const GemmShape& a0, const GemmShape& a1) {
   const GemmShape both[2] = {a0, a1};
-  const TilePlan b = plan_tiles(both, 2), p0 = plan_tiles(&a0, 1), p1 = plan_tiles(&a1, 1);
-  if (b.tile < 0) return p0.tile < 0 && p1.tile < 0;
-  return b.cost <= p0.cost + p1.cost;
+  const double b = plan_tiles(both, 2).cost, c0 = plan_tiles(&a0, 1).cost, c1 = plan_tiles(&a1, 1).cost;
+  return b == kNoCost ? c0 == kNoCost && c1 == kNoCost : b <= c0 + c1;
 }
 
 }  // namespace ff

@@ -4,7 +4,7 @@
 // bf16: 256-row workgroup tiles of v_mfma_f32_16x16x32_bf16 (k_gemm_pp) where the grid fills
 // the card, 64- and 128-row tiles of v_mfma_f32_32x32x16_bf16 whose waves split K (k_gemm_ks) on
 // small grids.  Both stream operands global -> LDS directly; a register-staged kernel (padded LDS
-// rows, double buffer) takes what they cannot: fewer stages than they need, operand rows too far apart.
+// rows, double buffer) takes large grids at K <= 256 and operand rows too far apart for the DMA.
 // fp32: fp32 MFMAs on 16x16, 32x32 or 64x64 tiles, the waves of a tile splitting K.
 #include "dev_common.h"
 #include "gemm_plan.h"
@@ -225,7 +225,7 @@ __device__ __forceinline__ int tile_of(int bid, int tm0, int tn0, int tm1, int t
 }
 
 // ------------------------------------------------------------------ bf16 MFMA GEMM
-// Register-staged fallback (K below the other kernels' three stages): BM x BN workgroup tile, BK = 64 per LDS stage
+// Register-staged (large grids at short K, any operand strides): BM x BN workgroup tile, BK = 64 per LDS stage
 // with padded rows, wavefront tiles WM x WN of v_mfma_f32_32x32x16_bf16.
 constexpr int BK = 64, LDT = BK + 8;
 
@@ -353,6 +353,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
 // for both groups, and the DMA that overwrites one starts after a barrier that every wave
 // passes with its reads of it complete.
 // Reading one phase ahead (fragments double-buffered) was no faster: 1317 against 1337 TFLOP/s.
+// Operand loads with sc0 | sc1 (past the L1) make no difference here or in k_gemm_ks: DiT-XL/2 block at
+// batch 8 135.7 against 135.7 us, FLUX-like double block 1201 against 1201.
 //
 // K % 64 != 0 (K % 8 == 0): the chunks of the last stage past K are loaded from the row's
 // first chunk of that stage (in bounds) and their fragments are zeroed in registers.
@@ -594,7 +596,8 @@ __global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {
 // Measured against the former kernel's best tile, us: M = 2048 N = 1152 K = 4608 37.3 -> 29.7,
 // K = 1152 15.4 -> 13.6; M = 256 K = 4608 26.7 -> 12.9; M = 1024 N = 3456 K = 1152 18.4 -> 14.1;
 // M = 1536 N = 3072 K = 15360 203 -> 174 (128x192, against 256x128 tiles of the kernel above).
-template <int BM, int BN, int NST, int EPI, bool OUT_F32, bool RES_F32, int NP>
+// SHORT: at most NST stages, all issued at once.
+template <int BM, int BN, int NST, bool SHORT, int EPI, bool OUT_F32, bool RES_F32, int NP>
 __global__ __launch_bounds__(512) void k_gemm_ks(GemmGroup<NP> G) {
 #ifdef __HIP_DEVICE_COMPILE__   // the host pass needs the launch stub only
   constexpr int TM = BM / 64, TN = BN / 32, PN = BN <= 128 ? BN : BN / 2;   // PN: columns of an epilogue pass
@@ -694,24 +697,36 @@ __global__ __launch_bounds__(512) void k_gemm_ks(GemmGroup<NP> G) {
       asm volatile("s_barrier" ::: "memory");
     };
 #define FF_KS_BACK() do { _Pragma("unroll") for (int j = 0; j < PER; ++j) vo[j] -= back[j]; } while (0)
-    // nk >= NST (host check): the prologue's stages are none of them the last
+    if constexpr (SHORT) {   // nk <= NST (host check): every stage has a buffer of its own
+      for (int kt = 0; kt < nk - 1; ++kt) issue();
+      FF_KS_BACK();
+      issue();
+      wait_vm<0>();
+      asm volatile("s_barrier" ::: "memory");
+      if (GRP) asm volatile("s_barrier" ::: "memory");   // the second group runs half a stage behind
+      for (int kt = 0; kt < nk; ++kt) {
+        mem(false, kt == nk - 1, Int<0>{});
+        mma();
+      }
+    } else {   // nk >= NST (host check): the prologue's stages are none of them the last
 #pragma unroll
-    for (int s = 0; s < NST - 1; ++s) issue();
-    wait_vm<(NST - 2) * PER>();
-    asm volatile("s_barrier" ::: "memory");
-    if (GRP) asm volatile("s_barrier" ::: "memory");   // the second group runs half a stage behind
-    for (int kt = 0; kt < nk - NST; ++kt) {
-      mem(true, false, Int<(NST - 2) * PER>{});
+      for (int s = 0; s < NST - 1; ++s) issue();
+      wait_vm<(NST - 2) * PER>();
+      asm volatile("s_barrier" ::: "memory");
+      if (GRP) asm volatile("s_barrier" ::: "memory");   // the second group runs half a stage behind
+      for (int kt = 0; kt < nk - NST; ++kt) {
+        mem(true, false, Int<(NST - 2) * PER>{});
+        mma();
+      }
+      FF_KS_BACK();
+      mem(true, false, Int<(NST - 2) * PER>{});   // issues the last stage
       mma();
+      static_for<0, NST - 1>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int later = NST - 3 - decltype(ic)::value;
+        mem(false, decltype(ic)::value == NST - 2, Int<(later > 0 ? later : 0) * PER>{});
+        mma();
+      });
     }
-    FF_KS_BACK();
-    mem(true, false, Int<(NST - 2) * PER>{});   // issues the last stage
-    mma();
-    static_for<0, NST - 1>([&](auto ic) __attribute__((always_inline)) {
-      constexpr int later = NST - 3 - decltype(ic)::value;
-      mem(false, decltype(ic)::value == NST - 2, Int<(later > 0 ? later : 0) * PER>{});
-      mma();
-    });
     if (!GRP) asm volatile("s_barrier" ::: "memory");
 #undef FF_KS_BACK
   };
@@ -1052,8 +1067,8 @@ constexpr bool grouped_epi(int epi, bool of, bool rf) { return epi == EPI_GATED 
 template <int TN, int EPI, bool OF, bool RF>
 void launch_pp(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(256, 64 * TN, 512, k_gemm_pp<TN); }
 
-template <int BM, int BN, int NST, int EPI, bool OF, bool RF>
-void launch_ks(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(BM, BN, 512, k_gemm_ks<BM, BN, NST); }
+template <int BM, int BN, int NST, bool SHORT, int EPI, bool OF, bool RF>
+void launch_ks(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(BM, BN, 512, k_gemm_ks<BM, BN, NST, SHORT); }
 
 template <int EPI, bool OF, bool RF>
 void launch_reg(const GemmArgs* a, int n, hipStream_t s) { FF_LAUNCH_GEMM(128, 128, 512, k_gemm_bf16<128, 128, 64, 32); }
@@ -1063,17 +1078,26 @@ GemmShape shape_of(const GemmArgs& a) { return GemmShape{a.M, a.N, a.K, a.lda, a
 template <int EPI, bool OF, bool RF>
 void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
   const GemmShape sh[2] = {shape_of(a[0]), shape_of(a[n - 1])};
+  const int nk = min_stages(sh, n);
   switch (plan_tiles(sh, n).tile) {
     case kTile256: launch_pp<4, EPI, OF, RF>(a, n, s); break;
     case kTile256x192: launch_pp<3, EPI, OF, RF>(a, n, s); break;
     case kTile256x128: launch_pp<2, EPI, OF, RF>(a, n, s); break;
-    case kTile128x192: launch_ks<128, 192, ks_nst(kTile128x192), EPI, OF, RF>(a, n, s); break;
-    case kTile128: launch_ks<128, 128, ks_nst(kTile128), EPI, OF, RF>(a, n, s); break;
-    case kTile128x96: launch_ks<128, 96, ks_nst(kTile128x96), EPI, OF, RF>(a, n, s); break;
-    case kTile128x64: launch_ks<128, 64, ks_nst(kTile128x64), EPI, OF, RF>(a, n, s); break;
-    case kTile64x96: launch_ks<64, 96, ks_nst(kTile64x96), EPI, OF, RF>(a, n, s); break;
-    case kTile64: launch_ks<64, 64, ks_nst(kTile64), EPI, OF, RF>(a, n, s); break;
-    case kTile64x32: launch_ks<64, 32, ks_nst(kTile64x32), EPI, OF, RF>(a, n, s); break;
+    case kTile128x192: launch_ks<128, 192, 4, false, EPI, OF, RF>(a, n, s); break;
+    case kTile128: launch_ks<128, 128, 5, false, EPI, OF, RF>(a, n, s); break;
+    case kTile128x96: launch_ks<128, 96, 4, false, EPI, OF, RF>(a, n, s); break;
+    case kTile128x64: launch_ks<128, 64, 4, false, EPI, OF, RF>(a, n, s); break;
+    case kTile64x96: launch_ks<64, 96, 4, false, EPI, OF, RF>(a, n, s); break;
+    case kTile64:   // fewer buffers where there are fewer stages
+      if (nk >= 5) launch_ks<64, 64, 5, false, EPI, OF, RF>(a, n, s);
+      else launch_ks<64, 64, 4, false, EPI, OF, RF>(a, n, s);
+      break;
+    case kTile64x32:
+      if (nk >= 6) launch_ks<64, 32, 6, false, EPI, OF, RF>(a, n, s);
+      else launch_ks<64, 32, 4, false, EPI, OF, RF>(a, n, s);
+      break;
+    case kTileShort64: launch_ks<64, 64, kShortStages, true, EPI, OF, RF>(a, n, s); break;
+    case kTileShort64x32: launch_ks<64, 32, kShortStages, true, EPI, OF, RF>(a, n, s); break;
     default: launch_reg<EPI, OF, RF>(a, n, s); break;
   }
 }

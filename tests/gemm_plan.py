@@ -16,12 +16,13 @@ extern "C" int tile(const int* a, const int* b) {
   const ff::GemmShape s[2] = {shape(a), shape(b ? b : a)};
   return ff::plan_tiles(s, b ? 2 : 1).tile;
 }
-static_assert(ff::kTileCount == 10, "TILES below");
+static_assert(ff::kTileReg == 12, "TILES below");
 extern "C" int grouped(const int* a, const int* b) { return ff::plan_grouped(shape(a), shape(b)); }
 """
 
-# in the order of the enum; -1 (the last) is the register-staged kernel
-TILES = ("256x256", "256x192", "256x128", "128x192", "128x128", "128x96", "128x64", "64x96", "64x64", "64x32", "reg")
+# in the order of the enum; "short" tiles take up to three 64-wide K stages, "reg" is the register-staged kernel
+TILES = ("256x256", "256x192", "256x128", "128x192", "128x128", "128x96", "128x64", "64x96", "64x64", "64x32",
+         "short 64x64", "short 64x32", "reg")
 
 
 @functools.lru_cache(maxsize=None)
@@ -71,3 +72,32 @@ def block_tiles(cfg):
     for name, n, k in (("qkv", 3 * C, C), ("proj", C, C), ("fc1", M, C), ("fc2", C, M)):
         put(name, [shape(B * s, n, k, seg=s, rows=r) for s, r in segs])
     return out
+
+
+def block_cfg(kind, d, H, B, lat, n_txt, ratio):
+    return dict(kinds=[kind], C=H * d, mlp=ratio * H * d, B=B, n_txt=n_txt,
+                n_img=lat[1] * (lat[2] // 2) * (lat[3] // 2))
+
+
+# Blocks of the GPU tests with the tiles that their GEMMs take: kind, heads (of 8 dims), batch, latent, text
+# rows, MLP ratio, launches
+SHORT_K = [
+    (synth.DIT, 2, 2, (4, 1, 26, 44), 0, 2,       # K = 16 / 32: one stage, part of it
+     "qkv short 64x32, proj short 64x32, fc1 short 64x32, fc2 short 64x32"),
+    (synth.DIT, 9, 8, (4, 1, 64, 64), 0, 2,       # K = 72 / 144: two and three stages
+     "qkv reg, proj short 64x32, fc1 short 64x64, fc2 short 64x32"),
+    (synth.DIT, 23, 8, (4, 1, 32, 60), 0, 2,      # K = 184: three stages, row tails
+     "qkv short 64x64, proj short 64x32, fc1 short 64x64, fc2 64x64"),
+    (synth.DIT, 31, 2, (4, 1, 64, 62), 0, 2,      # K = 248: four stages, fewer than the longest rings
+     "qkv 64x96, proj 64x32, fc1 64x64, fc2 64x32"),
+    (synth.DIT, 31, 16, (4, 1, 64, 62), 0, 1,     # K = 248, M = 15872
+     "qkv reg, proj reg, fc1 reg, fc2 reg"),
+    (synth.DIT, 21, 24, (4, 1, 44, 62), 0, 3,     # K = 168 / 504, M = 16368: three stages of 256 rows
+     "qkv 256x128, proj reg, fc1 256x128, fc2 64x96"),
+    (synth.MMDIT_DOUBLE, 15, 4, (4, 1, 40, 50), 13, 2,   # pairs, rows through a row map
+     "qkv short 64x64 x2, proj short 64x32 x2, fc1 short 64x32 x2, fc2 64x32 x2"),
+    (synth.MMDIT_DOUBLE, 23, 8, (4, 1, 64, 62), 13, 1,
+     "qkv reg x2, proj short 64x64 x2, fc1 short 64x64 x2, fc2 short 64x64 x2"),
+    (synth.MMDIT_SINGLE, 23, 4, (4, 1, 40, 50), 13, 2,   # bias and bias + GELU in one launch
+     "lin1 short 64x64 x2, lin2 64x32"),
+]

@@ -1,5 +1,8 @@
 """The host-side choice of the bf16 GEMM tiles (no GPU)."""
+import random
+
 import gemm_plan as g
+import pytest
 
 
 def test_stream_beyond_32_bit_offsets_leaves_the_other_its_tile():
@@ -21,3 +24,42 @@ def test_no_tile_for_one_problem_is_no_group():
     assert g.tile(far) == "reg" and g.tile(near) != "reg"
     assert g.tile(far, near) == "reg" and not g.grouped(far, near) and not g.grouped(near, far)
     assert g.grouped(far, far)   # neither has a tile of its own to lose
+
+
+def listed(case):
+    kind, H, B, lat, n_txt, ratio, tiles = case
+    return g.block_tiles(g.block_cfg(kind, 8, H, B, lat, n_txt, ratio)), tiles.split(", ")
+
+
+@pytest.mark.parametrize("case", g.SHORT_K)
+def test_blocks_take_the_listed_tiles(case):
+    """The GPU tests' blocks run the kernels that they are there for."""
+    got, want = listed(case)
+    assert got == want
+
+
+def test_short_k_on_a_small_grid_takes_a_small_tile():
+    """Up to three stages of K: 256-row tiles only where they are not a handful on the whole card."""
+    for K in range(8, 200, 8):
+        for M in (1, 15, 64, 256, 512, 1024, 2048):
+            for N in (8, 64, 192, 576):
+                t = g.tile(g.shape(M, N, K))
+                assert t.startswith("short") or (t == "reg" and M > 1024), (M, N, K, t)
+
+
+def test_tiles_have_the_stages_they_need():
+    """Whatever the sizes: the kernels' prologues take stages that are there, the short tiles no more than
+    they have buffers for."""
+    rng = random.Random(5)
+    log = lambda lo, hi: int(lo * (hi / lo) ** rng.random())
+    for _ in range(20000):
+        K = 8 * log(1, 600)
+        a = g.shape(log(1, 200000), 8 * log(1, 2000), K)
+        pair = g.shape(log(1, 5000), 8 * log(1, 2000), K) if rng.random() < 0.3 else None
+        t, nk = g.tile(a, pair), -(-K // 64)
+        if t.startswith("short"):
+            assert nk <= 3
+        elif t == "reg":
+            assert K <= 256
+        else:
+            assert nk >= (3 if t.startswith("256x") else 5 if t == "128x128" else 4), (K, t)

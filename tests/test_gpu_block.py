@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import gemm_plan
 import oracle as O
 import synth
 from paper_2607_27842_amd import abi, pipeline
@@ -344,3 +345,22 @@ def test_block_fp32_tiles(kind, H, d, B, lat, n_txt):
     cfg = ragged_cfg(kind, synth.F32, d=d, H=H, n_txt=n_txt, B=B, lat=lat)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
     check_block(cfg, W, seed=H)
+
+
+@pytest.mark.parametrize("kind,H,B,lat,n_txt,ratio", [c[:6] for c in gemm_plan.SHORT_K])
+def test_block_gemm_short_k(kind, H, B, lat, n_txt, ratio):
+    """GEMMs of one to four K stages: a part of a stage, fewer stages than buffers, the register-staged
+    kernel on large grids, pairs."""
+    need_gpu()
+    cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat, mlp_ratio=ratio)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
+    # matrices of N(0, 0.02^2) at these widths leave the update far below the rounding of h: scaled (by a
+    # power of two, exact in bf16) so that a product keeps its input's size
+    up = np.float32(2.0 ** round(np.log2(1 / (0.02 * np.sqrt(cfg["C"])))))
+    for s in ([W["txt"], W["img"]] if kind == synth.MMDIT_DOUBLE else [W]):
+        for k in s:
+            if k.endswith("_w") and k != "mod_w":
+                s[k] = s[k] * up
+    n = cfg["n_img"] + n_txt
+    rows = np.array(sorted({0, 1, n_txt, n_txt + 1, 14, 63, 64, 127, 128, 255, 256, n // 2, n - 2, n - 1} & set(range(n))))
+    check_block(cfg, W, seed=H, rows=rows)
