@@ -31,11 +31,33 @@ def listed(case):
     return g.block_tiles(g.block_cfg(kind, 8, H, B, lat, n_txt, ratio)), tiles.split(", ")
 
 
-@pytest.mark.parametrize("case", g.SHORT_K)
+@pytest.mark.parametrize("case", g.SHORT_K + g.OFF_64 + g.SPLIT_K + g.LARGE)
 def test_blocks_take_the_listed_tiles(case):
     """The GPU tests' blocks run the kernels that they are there for."""
     got, want = listed(case)
     assert got == want
+
+
+@pytest.mark.parametrize("name", g.IN_WORDS)
+def test_blocks_take_the_tiles_that_their_tests_state(name):
+    kind, d, H, B, lat, ratio, tiles = g.IN_WORDS[name]
+    assert g.block_tiles(g.block_cfg(kind, d, H, B, lat, 0, ratio)) == tiles.split(", ")
+
+
+@pytest.mark.parametrize("name", g.REFRESH)
+def test_history_is_refreshed_from_the_listed_tile(name):
+    kind, d, H, B, lat, n_txt, ratio, last = g.REFRESH[name]
+    assert g.block_tiles(g.block_cfg(kind, d, H, B, lat, n_txt, ratio))[-1] == last
+
+
+def test_listed_blocks_reach_every_tile():
+    """Each tile with the plain and the gated epilogue, and in one launch for two problems."""
+    seen = {(t.split(" ", 1)[0] in ("proj", "fc2", "lin2"), t.split(" ", 1)[1])
+            for case in g.SHORT_K + g.OFF_64 + g.SPLIT_K + g.LARGE for t in listed(case)[1]}
+    for t in g.TILES:
+        assert (False, t) in seen or (False, t + " x2") in seen, t
+        assert (True, t) in seen or (True, t + " x2") in seen, t
+        assert (False, t + " x2") in seen or (True, t + " x2") in seen, t
 
 
 def test_short_k_on_a_small_grid_takes_a_small_tile():

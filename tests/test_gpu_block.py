@@ -147,9 +147,8 @@ def test_mmdit_block_full_shape_sampled_rows(name, kind):
 
 
 def test_dit_block_gemm_tile_paths():
-    """A DiT block whose GEMMs take the 32-wide K-stage paths: qkv and fc1 256x256 tiles
-    (K = 2080 is not a multiple of 64), proj 128x128; fc2 (K = 8320, 64-wide stages) 128x96
-    tiles with two k groups of waves; attention with head dim 104."""
+    """A DiT block with K = 2080, half a stage past the 64 grid: qkv takes 256x256 tiles, fc1
+    256x192, proj and fc2 (K = 8320) 128x192; attention with head dim 104."""
     need_gpu()
     cfg = ragged_cfg(synth.DIT, synth.BF16, d=104, H=20, B=2, lat=(4, 1, 64, 64), mlp_ratio=4)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
@@ -159,8 +158,7 @@ def test_dit_block_gemm_tile_paths():
 
 def test_dit_block_ragged_wide_tiles():
     """A DiT block with 2000 token rows (ragged against both the 256- and 128-row tiles):
-    fc1 (N = 4608) takes 256x192 tiles, proj and fc2 128x96 tiles with four 64-wide K
-    stages and two k groups of waves, qkv two 128x128 tiles per CU."""
+    fc1 (N = 4608) takes 256x192 tiles, qkv 256x128, proj and fc2 128x96."""
     need_gpu()
     cfg = ragged_cfg(synth.DIT, synth.BF16, d=72, H=16, B=4, lat=(4, 1, 50, 40), mlp_ratio=4)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
@@ -170,8 +168,8 @@ def test_dit_block_ragged_wide_tiles():
 
 def test_dit_block_c2048_tiles():
     """A DiT block with C = 2048 (16 heads of 128) and 2048 rows: qkv takes 256x192 and fc1
-    256x256 tiles with 64-wide stages, proj and fc2 (N = 2048, 256 tiles) one 128x128 tile
-    per CU with four 64-wide stages and two k groups; attention with head dim 128."""
+    256x256 tiles, proj (N = 2048, 256 tiles) one 128x128 tile per CU, fc2 128x192; attention
+    with head dim 128."""
     need_gpu()
     cfg = ragged_cfg(synth.DIT, synth.BF16, d=128, H=16, B=2, lat=(4, 1, 64, 64), mlp_ratio=4)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
@@ -181,9 +179,9 @@ def test_dit_block_c2048_tiles():
 
 
 def test_dit_block_attention_wide_ragged():
-    """Head dim 128 on the 8-wavefront attention grid (4 query blocks x 16 heads x 4
-    samples = 256 workgroups, 128-key tiles): 1000 tokens per sample, so the last query
-    block holds 232 queries and the last key tile 104 keys."""
+    """Head dim 128 with 32 queries per wave (4 query blocks of 256 x 16 heads x 4 samples =
+    256 workgroups): 1000 tokens per sample, so the last query block holds 232 queries and
+    the last 64-key tile 40 keys."""
     need_gpu()
     cfg = ragged_cfg(synth.DIT, synth.BF16, d=128, H=16, B=4, lat=(4, 1, 50, 80), mlp_ratio=4)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
@@ -193,8 +191,7 @@ def test_dit_block_attention_wide_ragged():
 
 def test_dit_block_narrow_tiles():
     """A DiT block with 510 token rows (two samples of 255 tokens; the last 128-row tile
-    holds 126): qkv, proj and fc2 take 128x64 tiles and fc1 128x96 tiles, both with two k
-    groups of waves, so the gated epilogue runs on the 128x64 path too."""
+    holds 126): qkv takes 128x64 tiles, fc1 128x96, proj and fc2 64x64."""
     need_gpu()
     cfg = ragged_cfg(synth.DIT, synth.BF16, d=72, H=16, B=2, lat=(4, 1, 30, 34), mlp_ratio=4)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
@@ -225,21 +222,25 @@ def test_flux_block_rope_full_shape_sampled_rows(kind):
     check_block(cfg, W, rows=np.array(SAMPLE_ROWS["flux"]))
 
 
-@pytest.mark.parametrize("kind,H,B,lat,n_txt", [
-    (synth.DIT, 33, 32, (4, 1, 28, 64), 0),            # K = 264 / 528, M = 14336: 256x256 tiles
-    (synth.DIT, 33, 20, (4, 1, 32, 64), 0),            # M = 10240: 256x192 tiles
-    (synth.DIT, 23, 3, (4, 1, 26, 44), 0),             # K = 184 (three stages) / 368, M = 858: 256x128 tiles, row tail
-    (synth.DIT, 31, 1, (4, 1, 6, 10), 0),              # K = 248 / 496, M = 15: one short row tile
-    (synth.MMDIT_DOUBLE, 25, 3, (4, 1, 18, 22), 13),   # K = 200 / 400, text rows of three samples in one tile
-    (synth.MMDIT_SINGLE, 35, 2, (4, 1, 20, 30), 21),   # K = 280 / 840: odd and even stage counts
-])
+@pytest.mark.parametrize("kind,H,B,lat,n_txt", [c[:5] for c in gemm_plan.OFF_64])
 def test_block_gemm_tiles_off_the_64_grid(kind, H, B, lat, n_txt):
-    """K not a multiple of 64 takes the 256-row GEMM tiles at every grid size (three stages
-    and more, a partial last stage, row and column tails, rows through a row map)."""
+    """K not a multiple of 64: a partial last stage in the 256-row tiles (large grids) and the smaller
+    ones, row and column tails, rows through a row map."""
     need_gpu()
     cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
     check_block(cfg, W, seed=H)
+
+
+@pytest.mark.parametrize("kind,H,B,lat,n_txt,ratio", [c[:6] for c in gemm_plan.LARGE])
+def test_block_gemm_large_pairs_off_the_64_grid(kind, H, B, lat, n_txt, ratio):
+    """Both streams of a double block, or both parts of a single block's first projection, in one launch
+    of 256- and 128-row tiles, with a partial last K stage and tiles across samples."""
+    need_gpu()
+    cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat, mlp_ratio=ratio)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
+    n = cfg["n_img"] + n_txt
+    check_block(cfg, W, seed=H, rows=np.array([0, n_txt - 1, n_txt, 127, 128, 200, 255, 256, 300, n - 100, n - 2, n - 1]))
 
 
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
@@ -278,15 +279,7 @@ def test_block_qk_norm_rotated_rows_walked(dtype, kind, d, H, axes):
     check_block(cfg, W, seed=d, rows=np.array([0, 12, 13, 14, 31, 200, 372, 373, 500, 731, 732]))
 
 
-@pytest.mark.parametrize("kind,H,B,lat,n_txt", [
-    (synth.DIT, 33, 1, (4, 1, 22, 60), 0),              # M = 330, K = 264 (five stages: the least for 64x64) / 528: 64x64, 64x32
-    (synth.DIT, 49, 3, (4, 1, 40, 50), 0),              # M = 1500, K = 392 / 784: 128x64, 64x64, 64x96
-    (synth.DIT, 65, 3, (4, 1, 56, 50), 0),              # M = 2100, K = 520 / 1040: 128x128, two 64x96 per CU
-    (synth.DIT, 89, 2, (4, 1, 52, 100), 0),             # M = 2600, K = 712 / 1424: 128x192 (two epilogue passes), 128x128, 128x64
-    (synth.DIT, 144, 8, (4, 1, 32, 30), 0),             # M = 1920, K = 1152 / 2304: 128x96
-    (synth.MMDIT_DOUBLE, 49, 4, (4, 1, 18, 22), 13),    # text and image rows of four samples through a row map
-    (synth.MMDIT_SINGLE, 41, 1, (4, 1, 20, 30), 7),     # K = 328 / 984, bias and bias + GELU in one launch
-])
+@pytest.mark.parametrize("kind,H,B,lat,n_txt", [c[:5] for c in gemm_plan.SPLIT_K])
 def test_block_gemm_tiles_split_k(kind, H, B, lat, n_txt):
     """The GEMM tiles whose waves split K, small grids: row, column and K tails, the fewest
     stages of a tile, grouped problems."""
@@ -307,6 +300,8 @@ def test_block_gemm_tiles_split_k(kind, H, B, lat, n_txt):
     (128, 2, 1, (4, 1, 50, 62)),    # 775 keys
     (128, 8, 24, (4, 1, 18, 30)),   # 135 keys over 192 heads: 32 queries per wave
     (72, 8, 24, (4, 1, 34, 30)),    # 255 keys over 192 heads: 32 queries per wave
+    (96, 8, 24, (4, 1, 34, 30)),    # the same at the 96-wide tiles
+    (88, 8, 24, (4, 1, 18, 30)),    # and padded to them, 135 keys
 ])
 def test_block_attention_tiles(d, H, B, lat):
     """Attention at the edges of its 64-key tiles and query blocks, for every head-dim class."""

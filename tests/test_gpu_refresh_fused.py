@@ -4,11 +4,13 @@ when the history holds block outputs).  At a refresh step every layer is exact, 
 per-layer traces give each layer's input u (the previous layer's output) and output h:
 the slot the loop wrote must equal ff_cache_update(u, h) bit for bit.  Shapes are ragged
 against the GEMM tiles (rows and columns cut at the ends), for DiT blocks and for MMDiT
-double (text, then image stream) and single blocks."""
+double (text, then image stream) and single blocks, over the tiles whose epilogues differ
+(two passes of 128x192, one of the other tiles that split K, 256-row tiles, register-staged)."""
 import numpy as np
 import pytest
 import torch
 
+import gemm_plan
 import synth
 from paper_2607_27842_amd import abi, pipeline
 from gpu_util import need_gpu, say
@@ -16,7 +18,7 @@ from gpu_util import need_gpu, say
 pytestmark = pytest.mark.gpu
 
 CASES = {
-    # 3 x 90 = 270 rows; C = 240: the 96-wide column tiles of the gated GEMMs end half full
+    # 3 x 90 = 270 rows; C = 240 (64x32 tiles, the last column tile half full)
     "dit_ragged": lambda: synth.get_config("tiny", kinds=[synth.DIT] * 4, dtype=synth.BF16, C=240, H=5, d=48,
                                            mlp=960, lat=(4, 1, 20, 18), n_img=90, B=3, T=4, R=2),
     # text rows first; C = 256 with 24 + 90 rows per sample
@@ -24,6 +26,15 @@ CASES = {
                                       C=256, H=2, d=128, mlp=1024, n_txt=24, lat=(16, 1, 20, 18), n_img=90,
                                       B=2, T=4, R=2, sites=[1], dtype=synth.BF16),
 }
+
+
+def _large(kind, d, H, B, lat, n_txt, ratio, _):
+    """Two layers whose last GEMM takes the tile of the case's name, ragged in rows, columns and K."""
+    return synth.get_config("tiny", kinds=[kind] * 2, dtype=synth.BF16, C=H * d, H=H, d=d, mlp=ratio * H * d, lat=lat,
+                            n_img=(lat[2] // 2) * (lat[3] // 2), n_txt=n_txt, B=B, T=4, R=2, sites=[1])
+
+
+CASES.update({name: (lambda c=c: _large(*c)) for name, c in gemm_plan.REFRESH.items()})
 
 
 @pytest.mark.parametrize("feature_mode", [abi.FF_RESIDUAL, abi.FF_OUTPUT])
