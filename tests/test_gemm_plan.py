@@ -3,6 +3,7 @@ import random
 
 import gemm_plan as g
 import pytest
+import synth
 
 
 def test_stream_beyond_32_bit_offsets_leaves_the_other_its_tile():
@@ -24,6 +25,13 @@ def test_no_tile_for_one_problem_is_no_group():
     assert g.tile(far) == "reg" and g.tile(near) != "reg"
     assert g.tile(far, near) == "reg" and not g.grouped(far, near) and not g.grouped(near, far)
     assert g.grouped(far, far)   # neither has a tile of its own to lose
+
+
+@pytest.mark.parametrize("n_txt,want", [(1, "reg"), (8, "64x32")])
+def test_blocks_with_rows_beyond_32_bit_offsets(n_txt, want):
+    """The tiles of the GPU test's fc2: the text stream's, then the image stream's own."""
+    fc2 = [t for t in g.block_tiles(g.block_cfg(synth.MMDIT_DOUBLE, 8, 8, 32, (4, 1, 32, 676), n_txt, 192)) if t.startswith("fc2")]
+    assert len(fc2) == 2 and fc2[0] == "fc2 " + want and fc2[1].startswith("fc2 256x")
 
 
 def listed(case):

@@ -42,7 +42,8 @@ def run_block(cfg, W, u_np, c_np, rows=None):
     h2 = torch.empty_like(u)
     abi.ff_block_exact(m, 0, lw, c.data_ptr(), u.data_ptr(), h2.data_ptr(), ws.data_ptr(), ws_bytes)
     torch.cuda.synchronize()
-    assert torch.equal(h, h2), "exact block is not deterministic"
+    bits = torch.int16 if dt == torch.bfloat16 else torch.int32   # (NaN included)
+    assert torch.equal(h.view(bits), h2.view(bits)), "exact block is not deterministic"
     return host(h)
 
 
@@ -53,6 +54,16 @@ def boosted(W, kind):
         s["mod_w"] = (s["mod_w"] * 8).astype(np.float32)
         return s
     return {k: b(v) for k, v in W.items()} if kind == synth.MMDIT_DOUBLE else b(W)
+
+
+def grown(W, cfg):
+    # matrices of N(0, 0.02^2) at small widths leave the update far below the rounding of h: scaled (by a
+    # power of two, exact in bf16) so that a product keeps its input's size
+    up = np.float32(2.0 ** round(np.log2(1 / (0.02 * np.sqrt(cfg["C"])))))
+    for s in ([W["txt"], W["img"]] if cfg["kinds"][0] == synth.MMDIT_DOUBLE else [W]):
+        for k in s:
+            if k.endswith("_w") and k != "mod_w":
+                s[k] = s[k] * up
 
 
 def check_block(cfg, W, seed=0, rows=None, tol=None):
@@ -349,13 +360,82 @@ def test_block_gemm_short_k(kind, H, B, lat, n_txt, ratio):
     need_gpu()
     cfg = ragged_cfg(kind, synth.BF16, d=8, H=H, n_txt=n_txt, B=B, lat=lat, mlp_ratio=ratio)
     W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), kind)
-    # matrices of N(0, 0.02^2) at these widths leave the update far below the rounding of h: scaled (by a
-    # power of two, exact in bf16) so that a product keeps its input's size
-    up = np.float32(2.0 ** round(np.log2(1 / (0.02 * np.sqrt(cfg["C"])))))
-    for s in ([W["txt"], W["img"]] if kind == synth.MMDIT_DOUBLE else [W]):
-        for k in s:
-            if k.endswith("_w") and k != "mod_w":
-                s[k] = s[k] * up
+    grown(W, cfg)
     n = cfg["n_img"] + n_txt
     rows = np.array(sorted({0, 1, n_txt, n_txt + 1, 14, 63, 64, 127, 128, 255, 256, n // 2, n - 2, n - 1} & set(range(n))))
     check_block(cfg, W, seed=H, rows=rows)
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("d,H,B,lat,row", [
+    (64, 3, 2, (4, 1, 18, 30), 0),      # 135 keys: the first tile
+    (72, 4, 2, (4, 1, 26, 24), 155),    # 156 keys: the last key, in a tile with 28
+    (128, 2, 2, (4, 1, 18, 30), 70),    # a tile in the middle
+    (72, 14, 8, (4, 1, 40, 30), 299),   # 32 queries per wave in bf16
+])
+def test_block_attention_nan_key(dtype, d, H, B, lat, row):
+    """A NaN in one row of sample 0 makes its key NaN, so every row of that sample's output is NaN; the other
+    samples keep their bits."""
+    need_gpu()
+    cfg = ragged_cfg(synth.DIT, dtype, d=d, H=H, B=B, lat=lat, mlp_ratio=1)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.DIT)
+    bf = dtype == synth.BF16
+    u = synth.normal((B, cfg["n_img"], cfg["C"]), 17, bf16=bf)
+    c = synth.normal((B, cfg["C"]), 18)
+    clean = run_block(cfg, W, u, c)
+    u[0, row, 5] = np.nan
+    got = run_block(cfg, W, u, c)
+    assert np.isnan(got[0]).all()
+    assert np.array_equal(got[1:], clean[1:])
+
+
+@pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
+@pytest.mark.parametrize("d,H,lat,live", [
+    (64, 3, (4, 1, 40, 20), slice(150, 200)),    # 200 keys: two tiles without a finite score before the first
+    (64, 3, (4, 1, 40, 20), slice(3, 4)),        # one key, in the first tile
+    (128, 2, (4, 1, 40, 20), slice(199, 200)),   # the last key alone
+    (72, 4, (4, 1, 16, 16), slice(0, 64)),       # all of one tile
+    (40, 3, (4, 1, 24, 22), slice(64, 128)),     # a tile between two without
+])
+def test_block_attention_scores_below_the_range(dtype, d, H, lat, live):
+    """Scores of -1e40 (-inf in fp32) but for the keys `live`, whose scores are 0: probabilities of exactly 0
+    and 1 / n, also while no key tile has had a finite score.  q is 1e20 in each head's first dim, k is
+    1e20 times the normalised first channel, which is 0 in the live rows and negative in the others (their
+    first two channels cancel, so that the row mean is 0 without rounding)."""
+    need_gpu()
+    cfg = ragged_cfg(synth.DIT, dtype, d=d, H=H, B=1, lat=lat, mlp_ratio=1)
+    C, n, bf = cfg["C"], cfg["n_img"], dtype == synth.BF16
+    fix = synth.to_bf16_values if bf else (lambda a: a)
+    W = synth.make_layer_weights(cfg, 0, bias_std=0.02)
+    W["mod_w"] = np.zeros_like(W["mod_w"])
+    W["mod_b"] = np.zeros_like(W["mod_b"])
+    W["mod_b"][2 * C:3 * C] = W["mod_b"][5 * C:] = 1   # gates 1, no shift, no scale
+    big = float(fix(np.array([1e20], np.float32))[0])
+    W["qkv_w"][:2 * C] = 0
+    W["qkv_b"][:2 * C] = 0
+    W["qkv_b"][:C:d] = big
+    W["qkv_w"][C:2 * C:d, 0] = big
+    # the rounding of h, up to 2^-7 for 2 <= |h| < 4 in bf16, is 6 % of the update without these factors
+    W["qkv_w"][2 * C:] *= 8
+    W["o_w"] = W["o_w"] * 8
+    half = np.random.default_rng(3).integers(-24, 25, size=(1, n, C // 2)).astype(np.float32) / 8   # exact sums
+    u = np.stack([half, -half], -1).reshape(1, n, C)
+    u[0, :, 0], u[0, :, 1] = -2, 2
+    u[0, live, 0] = u[0, live, 1] = 0
+    c = synth.normal((1, C), 19)
+    got = run_block(cfg, W, u, c)
+    ref = O.block(synth.DIT, u.astype(np.float64), O.silu(c.astype(np.float64)), W, cfg)
+    err = O.max_rel_err(got - u, (O.round_bf16(ref) if bf else ref) - u)
+    say(f"  d={d} live={live}: err(h-u)={err:.3e}")
+    assert np.isfinite(got).all() and err <= TOL[dtype], err
+
+
+@pytest.mark.parametrize("n_txt", [1, 8])
+def test_block_rows_beyond_32_bit_offsets(n_txt):
+    """fc2 of the text stream, whose samples lie 5409 and more rows of 12 288 elements apart: 256 rows span
+    more than 4 GB.  One text row a sample leaves no tile (the register-staged kernel), eight a 64-row one."""
+    need_gpu()
+    cfg = ragged_cfg(synth.MMDIT_DOUBLE, synth.BF16, d=8, H=8, n_txt=n_txt, B=32, lat=(4, 1, 32, 676), mlp_ratio=192)
+    W = boosted(synth.make_layer_weights(cfg, 0, bias_std=0.02, gain_std=0.1), synth.MMDIT_DOUBLE)
+    grown(W, cfg)
+    check_block(cfg, W, seed=n_txt, rows=np.array([0, n_txt - 1, n_txt, 255, 3000, 5407 + n_txt]))
