@@ -784,7 +784,7 @@ def main():
     achieved = g["flops"] / (g["ms"] / 1e3) / 1e12
     roof = {"bound": "mfma", "achieved": round(achieved, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": gemm_traffic(),
-            "kernel": "k_gemm_dl64 / k_gemm_dl / k_gemm_bf16 (all exact-block GEMM launches of one FeatFix loop)",
+            "kernel": "k_gemm_pp / k_gemm_ks / k_gemm_bf16 (all exact-block GEMM launches of one FeatFix loop)",
             "avg_launch_us": round(g["ms"] * 1e3 / g["launches"], 3),
             "flop_per_launch": g["flops"] / g["launches"]}
     hbm = hbm_rates(kern)

@@ -54,9 +54,9 @@ constexpr ShortCost kShortCost[3] = {{kTileShort64, 64, 64, 4.2, 0.0058, 4.0, 0.
                                      {kTileShort64x32, 64, 32, 3.8, 0.0050, 4.0, 0.56, 0.0016},
                                      {kTileReg, 128, 128, 4.4, 0.0170, 4.4, 0.50, 0.0135}};
 
-inline long tiles_of(const GemmShape* a, int n, int bm, int bn) {
+inline long tiles_of(const GemmShape* a, int n, unsigned bm, unsigned bn) {
   long t = 0;
-  for (int i = 0; i < n; ++i) t += (long)((a[i].M + bm - 1) / bm) * ((a[i].N + bn - 1) / bn);
+  for (int i = 0; i < n; ++i) t += (long)(((unsigned)a[i].M + bm - 1) / bm) * (((unsigned)a[i].N + bn - 1) / bn);
   return t;
 }
 
@@ -85,17 +85,19 @@ inline TilePlan plan_tiles(const GemmShape* a, int n) {
   const int nk = min_stages(a, n);
   int K = 0;
   for (int i = 0; i < n; ++i) K = std::max(K, a[i].K);
+  const bool near = dma_ok(a, n, 256, 256);   // then every tile's rows are
   for (int c = 0; c < kTileCount; ++c) {
     if (nk < (c <= kTile256x128 ? 3 : c == kTile128 ? 5 : 4)) continue;   // the stages that the kernel's prologue takes
     const TileCost& t = kTileCost[c];
-    if (!dma_ok(a, n, t.bm, t.bn)) continue;
+    if (!near && !dma_ok(a, n, t.bm, t.bn)) continue;
     const long tiles = tiles_of(a, n, t.bm, t.bn), slots = t.lat2 > 0 ? 512 : 256, rest = tiles % slots;
     const double one = t.lat + t.k * K, full = t.lat2 > 0 ? t.lat2 + t.k2 * K : one;
     const double cost = std::max(tiles / slots * full + (rest == 0 ? 0 : rest <= 256 ? one : full), tiles / 256.0 * t.pow * K);
     if (cost < best.cost) best = TilePlan{c, cost};
   }
+  if (K > kRegK) return best;
   for (const ShortCost& t : kShortCost) {
-    if (t.tile == kTileReg ? K > kRegK : K > 64 * kShortStages || !dma_ok(a, n, t.bm, t.bn)) continue;
+    if (t.tile != kTileReg && (K > 64 * kShortStages || !(near || dma_ok(a, n, t.bm, t.bn)))) continue;
     const double rounds = tiles_of(a, n, t.bm, t.bn) / 256.0;
     const double cost = std::max(t.lat + t.k * K, t.base + rounds * (t.tile_us + t.tile_k * K));
     if (cost < best.cost) best = TilePlan{t.tile, cost};

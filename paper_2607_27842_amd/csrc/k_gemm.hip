@@ -1080,6 +1080,8 @@ void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
   const GemmShape sh[2] = {shape_of(a[0]), shape_of(a[n - 1])};
   const int nk = min_stages(sh, n);
   switch (plan_tiles(sh, n).tile) {
+    case kTileShort64: launch_ks<64, 64, kShortStages, true, EPI, OF, RF>(a, n, s); break;
+    case kTileShort64x32: launch_ks<64, 32, kShortStages, true, EPI, OF, RF>(a, n, s); break;
     case kTile256: launch_pp<4, EPI, OF, RF>(a, n, s); break;
     case kTile256x192: launch_pp<3, EPI, OF, RF>(a, n, s); break;
     case kTile256x128: launch_pp<2, EPI, OF, RF>(a, n, s); break;
@@ -1096,8 +1098,6 @@ void launch_bf16(const GemmArgs* a, int n, hipStream_t s) {
       if (nk >= 6) launch_ks<64, 32, 6, false, EPI, OF, RF>(a, n, s);
       else launch_ks<64, 32, 4, false, EPI, OF, RF>(a, n, s);
       break;
-    case kTileShort64: launch_ks<64, 64, kShortStages, true, EPI, OF, RF>(a, n, s); break;
-    case kTileShort64x32: launch_ks<64, 32, kShortStages, true, EPI, OF, RF>(a, n, s); break;
     default: launch_reg<EPI, OF, RF>(a, n, s); break;
   }
 }
