@@ -125,7 +125,7 @@ SPLIT_K = [
     (synth.DIT, 65, 3, (4, 1, 56, 50), 0, 2,             # M = 2100, K = 520 / 1040: two 64x96 per CU
      "qkv 128x128, proj 64x96, fc1 64x96, fc2 64x96"),
     (synth.DIT, 89, 2, (4, 1, 52, 100), 0, 2,            # M = 2600, K = 712 / 1424: two epilogue passes of 128x192
-     "qkv 128x192, proj 128x64, fc1 128x128, fc2 64x64"),
+     "qkv 128x192, proj 128x64, fc1 128x128, fc2 128x64"),
     (synth.DIT, 144, 8, (4, 1, 32, 30), 0, 2,            # M = 1920, K = 1152 / 2304
      "qkv 256x128, proj 128x96, fc1 128x192, fc2 128x96"),
     (synth.MMDIT_DOUBLE, 49, 4, (4, 1, 18, 22), 13, 2,   # text and image rows of four samples through a row map
@@ -173,11 +173,11 @@ REFRESH = {
 # blocks whose tests say in words which tiles they take: kind, head dim, heads, batch, latent, MLP ratio, launches
 IN_WORDS = {
     "test_dit_block_gemm_tile_paths": (synth.DIT, 104, 20, 2, (4, 1, 64, 64), 4,
-                                       "qkv 256x256, proj 128x192, fc1 256x192, fc2 128x192"),
+                                       "qkv 256x256, proj 128x192, fc1 256x192, fc2 128x96"),
     "test_dit_block_ragged_wide_tiles": (synth.DIT, 72, 16, 4, (4, 1, 50, 40), 4,
                                          "qkv 256x128, proj 128x96, fc1 256x192, fc2 128x96"),
     "test_dit_block_c2048_tiles": (synth.DIT, 128, 16, 2, (4, 1, 64, 64), 4,
-                                   "qkv 256x192, proj 128x128, fc1 256x256, fc2 128x192"),
+                                   "qkv 256x192, proj 128x128, fc1 256x256, fc2 128x128"),
     "test_dit_block_narrow_tiles": (synth.DIT, 72, 16, 2, (4, 1, 30, 34), 4,
                                     "qkv 128x64, proj 64x64, fc1 128x96, fc2 64x64"),
 }
