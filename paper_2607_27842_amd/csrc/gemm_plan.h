@@ -13,7 +13,7 @@ struct GemmShape { int M, N, K, lda, ldw, seg, rows; };
 
 // Tile choice: the candidate with the least estimated time.  A round of workgroups takes
 // lat + k * K us, bound by its own chain of stages.  A grid takes at least pow us per 256 tiles and unit
-// of K: for the 256-row tiles the card's power limit (large grids: the clock falls to about 1.7 GHz, so
+// of K: for the 256-row tiles the card's power limit (large grids: the clock falls to about 1.9 GHz, so
 // that a grid that leaves CUs idle runs its tiles faster), for the others what the caches deliver at
 // long K, about (BM + BN) bytes * 2 * K per tile at 8 to 14 TB/s.  Tiles that leave room for a second
 // workgroup per CU take lat2 + k2 * K for a round of 257 to 512.

@@ -21,13 +21,13 @@ constexpr float kPLim = 256.0f;   // a lane's probability sum per query and tile
 // probabilities, and the DMA of the tiles three and two ahead) and an MFMA slot (the next
 // tile's scores, then this tile's P V), each ended by a barrier; the second group runs one
 // slot behind, so that on every SIMD one wave's VALU work meets the other's MFMAs.
-// What bounds it: the card's power limit on long sequences (clock 1.86 GHz at N = 14566, H =
-// 16, d = 128; fewer VALU instructions, no bank conflicts and earlier DMA took 7 % of the
-// cycles and none of the time).  Against the kernel this replaced (32x32x16 MFMAs, both waves
-// of a SIMD in phase, K and V staged through registers): N = 14566, H = 16, d = 128 1710 ->
-// 1460 us (1190 TFLOP/s), N = 4608, H = 24 267 -> 230, N = 1536, H = 24 62 -> 40, N = 3000, H =
-// 20, d = 96 100 -> 67, B = 2, N = 1668, H = 37, d = 40 105 -> 75, B = 8, N = 256, H = 16, d =
-// 72 8.7 -> 8.0.
+// What bounds it: the card's power limit on long sequences (N = 14566, H = 16, d = 128: clock 2.0 of
+// 2.4 GHz, MFMAs busy 58 % of its cycles, VALU work beside them in 35 % of those; fewer VALU
+// instructions, no bank conflicts and earlier DMA took 7 % of the cycles and none of the time).
+// Against the kernel this replaced (32x32x16 MFMAs, both waves of a SIMD in phase, K and V staged
+// through registers): N = 14566, H = 16, d = 128 1710 -> 1460 us (1190 TFLOP/s), N = 4608, H = 24
+// 267 -> 230, N = 1536, H = 24 62 -> 40, N = 3000, H = 20, d = 96 100 -> 67, B = 2, N = 1668, H = 37,
+// d = 40 105 -> 75, B = 8, N = 256, H = 16, d = 72 8.7 -> 8.0.
 // v_mfma_f32_16x16x32_bf16 layouts (A lane l: row l%16, k 8*(l/16)+0..7; B lane l: column
 // l%16, same k; D[v] at row 4*(l/16)+v, column l%16):
 //   S^T = K Q^T: lane l holds the scores of query l%16 at keys 16 i + 4 (l/16) + v, i < 4.

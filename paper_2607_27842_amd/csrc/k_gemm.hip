@@ -336,10 +336,10 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_gemm_bf16(GemmGr
 // 4 TN MFMAs, with a barrier after each.  The second group runs half a phase behind, so that
 // on every SIMD one wave's MFMAs cover the other's reads and DMA.
 //
-// What bounds it: on large grids the card's power limit.  With random operands the clock falls
-// to about 1.7 GHz while the MFMAs are busy 84 % of the cycles, so what counts is energy per
-// FLOP: v_mfma_f32_16x16x32_bf16 moves half the accumulator bytes per FLOP of the 32x32x16
-// form and runs 8 % faster in this same kernel (M = 4608, N = 21504, K = 3072: 496 -> 460 us;
+// What bounds it: on large grids the card's power limit.  With random operands the clock is 1.9 to
+// 2.0 GHz of 2.4 and the MFMAs are busy 69 % of its cycles (counters at M = 4608, N = 21504, K = 3072),
+// so what counts is energy per FLOP: v_mfma_f32_16x16x32_bf16 moves half the accumulator bytes per
+// FLOP of the 32x32x16 form and runs 8 % faster in this same kernel (the same shape: 496 -> 460 us;
 // one wait and barrier per stage with 32x32x16: 545 us).  On small grids it is bound by its
 // chain of stages: 0.96 us per stage of 256x256 against 0.85 us of MFMA time at 2.4 GHz.
 //
@@ -583,11 +583,14 @@ __global__ __launch_bounds__(512) void k_gemm_pp(GemmGroup<NP> G) {
 // Small grids, where 256-row tiles would leave CUs idle: BM x BN tile, 64-wide stages, 8 waves on
 // the two halves of the tile's rows and the four 16-wide k steps of a stage.
 //
-// What bounds it: LDS bandwidth.  A stage writes (BM + BN) * 128 bytes and reads (BM / 2 + BN) *
-// 256, at 128 bytes a cycle 544 cycles for 128x96, of which the MFMAs fill 386; measured 730.
-// The kernel before it split K over two groups only and read a 32-row block at a time (736 cycles
-// of LDS, 950 measured); deeper rings and prefetches into the L2 made that one slower, and
-// fragments straight from memory (16 rows x 64 bytes per load) run at a quarter of the L1's rate.
+// What bounds it: the memory part of a half stage (fragment reads, DMA, waits and the barrier), one
+// after the other; at long K on wide models also what the caches deliver.  A 128x96 stage takes 730
+// cycles (0.307 us at 2.4 GHz), of which the MFMAs fill 386; by the counters the LDS is busy with
+// fragment reads for 200, and the DMA writes 28 KB.  The kernel before it split K over two groups
+// only and read a 32-row block at a time (950 cycles); deeper rings and prefetches into the L2 made
+// that one slower, and fragments straight from memory (16 rows x 64 bytes per load) run at a quarter
+// of the L1's rate.  Rings of four stages for 64x64 and 64x32, where five and six fit, are slower
+// (DiT-XL/2 block of one image 58.6 -> 62.5 us).
 // Alternation: waves 0-3 and 4-7, one of each per SIMD, run half a stage apart, a barrier after
 // each half, so that one's MFMAs cover the other's fragment reads and DMA.  A stage's buffer is
 // refilled from the slot after its last read on (NST - 1 stages ahead); a wave waits for its own
